@@ -40,10 +40,11 @@ DEVICE_FLAGS = [
 
 
 # Per-file additions. The matrix-core register tile clears single
-# accumulator elements between operations; with the accumulators in
-# ordinary VGPRs that is one move per element instead of a round trip of
-# the whole accumulator through AGPRs.
+# accumulator elements between operations, and the matrix-core window sums
+# use every accumulator in vector code after a few operations; with the
+# accumulators in ordinary VGPRs neither needs a round trip through AGPRs.
 FILE_FLAGS = {
+    "interp_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "spread_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 

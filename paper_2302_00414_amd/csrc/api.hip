@@ -116,6 +116,8 @@ struct nfft_plan_s {
   int32_t* multi_first = nullptr;  // first itemp slot of each split tile
   int nmulti = 0;
   int nslots = 0;                  // itemp slots
+  int32_t* fwd_items = nullptr;    // forward window sums: [nfwd][4] first node, nodes, tile, 0
+  int nfwd = 0;
   int32_t* empty_bins = nullptr;   // tiles without nodes (their slots are never written)
   void* gpart = nullptr;           // spread mode 6 partials [max_rhs][slot][256]
   void* gft = nullptr;             // spread mode 6 node-major samples [groups of 32][N][32]
@@ -730,6 +732,29 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
     if (hc[b] == 0) ebins.push_back(b);
   p->nempty = (int)ebins.size();
   g.nsub = (int)istart.size();
+  // work items of the forward's window sums: runs of whole groups of 16
+  // nodes, at most kInterpItem, of one tile. In tile order, an eighth of them
+  // for each XCD (work-group i runs on XCD i mod 8): neighbouring tiles read
+  // the same grid lines through one L2.
+  std::vector<int32_t> fitem;
+  if (nfft::interp_mma_supported(d, g.T, p->prec == NFFT_F64, p->m)) {
+    std::vector<int32_t> it;
+    for (int b = 0; b < g.nbins; ++b) {
+      const int n = hc[b], k = (n + nfft::kInterpItem - 1) / nfft::kInterpItem;
+      for (int j = 0, s0 = 0; j < k; ++j) {
+        const int left = (n - s0 + 15) / 16;  // groups
+        const int c = std::min(n - s0, (left + k - j - 1) / (k - j) * 16);
+        it.insert(it.end(), {hstart[b] + s0, c, b, 0});
+        s0 += c;
+      }
+    }
+    const int n = (int)(it.size() / 4), per = (n + 7) / 8;
+    p->nfwd = 8 * per;
+    fitem.assign((size_t)4 * p->nfwd, 0);
+    for (int i = 0; i < n; ++i)
+      std::copy(it.begin() + 4 * i, it.begin() + 4 * i + 4,
+                fitem.begin() + 4 * ((i % per) * 8 + i / per));
+  }
   // launch order: largest work items first, so that the work-groups that
   // start last are the small remainders of tiles, in blocks of one item per
   // compute unit whose direction alternates: the first work-groups go one
@@ -810,6 +835,10 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   if (!ebins.empty())
     HIP_TRY(p, hipMemcpyAsync(p->empty_bins, ebins.data(), ebins.size() * 4, hipMemcpyHostToDevice, s));
 
+  if (!fitem.empty()) {
+    TRY(dalloc(p, &p->fwd_items, fitem.size() * sizeof(int32_t)));
+    HIP_TRY(p, hipMemcpyAsync(p->fwd_items, fitem.data(), fitem.size() * 4, hipMemcpyHostToDevice, s));
+  }
   TRY(dalloc(p, &p->w, N * sizeof(cplx<R>)));
   TRY(alloc_workspace<R>(p, s));
   TRY(build_tables<R>(p));
@@ -1092,6 +1121,8 @@ int run_forward(nfft_plan_t p, const void* fhat, void* f, int nrhs, hipStream_t 
   ia.item_start = p->item_start;
   ia.item_count = p->item_count;
   ia.item_bin = p->item_bin;
+  ia.items = p->fwd_items;
+  ia.nitems = p->nfwd;
   ia.coef = (const R*)p->coef;
   // the window factor table, where the plan has one (same values as the
   // polynomials), saves the per-call evaluation
@@ -1293,6 +1324,8 @@ int64_t nfft_footprint(int d, int M, double sigma, int m, int64_t N, int precisi
   bytes += R_ * ipow(Ms, d) * cb;                         // forward grid
   bytes += M * 8 + Ms * cb;                               // tables
   if (d == 2) bytes += N * 4 * m * rb;                    // window factors (spread mode 3)
+  if (nfft::interp_mma_supported(d, T, precision == NFFT_F64, m))
+    bytes += (nbins + N / nfft::kInterpItem + 8) * 16;    // forward work items
   return bytes;
 }
 

@@ -172,6 +172,8 @@ struct InterpArgs {
   const int32_t* item_start;
   const int32_t* item_count;
   const int32_t* item_bin;
+  const int32_t* items;      // matrix-core form: [nitems][4] first node, nodes (0: padding), tile, 0
+  int nitems;
   const R* coef;
   const R* psi;              // d = 2: window factor table [N][2m][2] in tile order, or null
   int64_t grid_rs;
@@ -181,6 +183,11 @@ struct InterpArgs {
 };
 template <typename R>
 hipError_t launch_interp(const InterpArgs<R>& a, int nrhs, hipStream_t s);
+// The same sums on the matrix cores (float32, d = 2, tile edge 16, m >= 5;
+// nodes row-sorted within tiles).
+constexpr int kInterpItem = 256;  // most nodes of one of its work items
+bool interp_mma_supported(int d, int T, bool f64, int m);
+hipError_t launch_interp_mma(const InterpArgs<float>& a, int nrhs, hipStream_t s);
 
 // ------------------------------------------------------------------- FFT
 enum LoadMode { kLoadMerge = 0, kLoadLine = 1, kLoadPadScaled = 2 };

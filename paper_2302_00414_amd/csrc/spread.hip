@@ -531,6 +531,9 @@ hipError_t launch_spread(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
 template <typename R>
 hipError_t launch_interp(const InterpArgs<R>& a, int nrhs, hipStream_t s) {
   if (a.g.nsub == 0) return hipSuccess;
+  if constexpr (std::is_same<R, float>::value) {
+    if (interp_mma_supported(a.g.d, a.g.T, false, a.g.m)) return launch_interp_mma(a, nrhs, s);
+  }
   switch (a.g.d) {
     case 1: NFFT_DISPATCH_M(interp_dm, R, 1, a, nrhs, s)
     case 2: NFFT_DISPATCH_M(interp_dm, R, 2, a, nrhs, s)
