@@ -625,7 +625,7 @@ def traffic_record(kernel):
 
 # sources of the d = 2 single-rhs spreading kernels
 SPREAD_SOURCES = ("spread.hip", "spread_common.hpp", "spread_group.hpp", "spread_pre.hip", "spread_late.hip",
-                  "spread_rows.hip", "spread_reg.hip", "spread_mma.hip")
+                  "spread_rows.hip", "spread_reg.hip", "spread_mma.hip", "spread_tile.hip")
 
 
 def spread_kernel_name(t):
@@ -637,7 +637,7 @@ def spread_kernel_name(t):
     if mode in (5, 7) and T == 16:
         nw = {256: 4, 512: 8}.get(t["spread_threads"], 2)
         if mode == 7:
-            return f"spread_mma_kernel<float, {MW}, {nw}>"
+            return f"spread_mma_kernel<float, {MW}, {nw}>" if nw > 2 else f"spread_tile_kernel<float, {MW}, 1>"
         return f"spread_reg_kernel<{MW}, {nw}>"
     ws = {3: 1, 4: 2}.get(mode, 0)   # window source of the group kernel
     return (f"spread_group_kernel<float, 2, {MW}, {t['spread_threads']}, "

@@ -99,12 +99,17 @@ int nfft_plan(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t N,
  *                             >= m; clipped to M_sigma (default: d = 1: 256,
  *                             d = 2: 16, d = 3: 8). Fixed at plan time.
  *   NFFT_TUNE_ITEM_NODES      most nodes in one spreading work item,
- *                             16..65536 (default 256). Fixed at plan time.
+ *                             16..65536 (default 256; left at the default,
+ *                             a plan whose default spread mode takes the
+ *                             kernel of mode 7 joins up to two). Fixed at
+ *                             plan time.
  *   NFFT_TUNE_SPREAD_THREADS  threads of a spreading work-group for d <= 2,
  *                             float32, one right-hand side per work-group:
  *                             64, 128 or 256 (default 128); 512 for spread
  *                             modes 5 and 7 (resolved to 256 for the others).
- *                             Float64 plans use it in spread mode 7 only.
+ *                             The float32 LDS kernels and mode 5 use it; in
+ *                             mode 7, float32 and one right-hand side it
+ *                             selects the shape (below).
  *   NFFT_TUNE_RHS_PER_GROUP   right-hand sides that one spreading work-group
  *                             takes when nrhs > 1 and d <= 2: 1, 2, 4 or 8
  *                             (default 1). Above 1 the node data and window
@@ -121,8 +126,11 @@ int nfft_plan(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t N,
  *                             2 = two groups per node, one for the real and
  *                             one for the imaginary plane (default 1).
  *   NFFT_TUNE_SPREAD_MODE     single right-hand-side spreading for d = 2:
- *                             1 = accumulation in LDS tiles, 2 = register
- *                             row sweep (nodes of a tile taken row by row,
+ *                             1 = accumulation in LDS tiles (as the default,
+ *                             with neither the mode nor the threads or planes
+ *                             set: the kernel of mode 7, there up to m = 8,
+ *                             where the nodes per tile make it the faster
+ *                             one), 2 = register row sweep (nodes of a tile taken row by row,
  *                             the rows a node reaches kept in registers;
  *                             needs T + 2m <= 32; resolved to 1 elsewhere).
  *                             3 = as 1, with the 2m window factors per
@@ -167,19 +175,25 @@ int nfft_plan(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t N,
  *                             group. Resolved to 5 (and so on) where not
  *                             supported.
  *                             7 = d = 2, tile edge 16, 2m + 1 <= 16, float32
- *                             or float64 (sums in float64 accumulators, in a
- *                             fixed order): the padded tile of a work item
- *                             on the matrix cores; the nodes of one tile row reach 16
- *                             padded rows, so four nodes at a time form a
- *                             16 x 32 block of products (rows held as
- *                             slots that shift with the tile row); the
- *                             waves' tiles are summed in a fixed order at
- *                             the end, and the output is the same padded
+ *                             or float64 (every cell in one sum of a fixed
+ *                             order, in float32 in runs that are added in
+ *                             float64): the padded tile of a work item
+ *                             on the matrix cores; the nodes of a few tile
+ *                             rows reach 16 padded rows, so four nodes at a
+ *                             time form a 16 x 32 block of products (rows
+ *                             held as slots that move down with the nodes);
+ *                             several right-hand sides of a call share the
+ *                             window factors. float32, one right-hand side:
+ *                             that with 64 or 128 threads; with 256 or 512
+ *                             four or eight waves each keep a padded tile
+ *                             of some of the groups of four, taken one tile
+ *                             row at a time, and sum them in float32 at the
+ *                             end in a fixed order. The output is the same padded
  *                             tile as modes 1 .. 5 write. Also float32,
  *                             d = 3, tile edge 8, 2m <= 8: one wave holds
  *                             the padded 3-D tile (one 16 x 16 block per
  *                             plane) and takes four nodes of one tile row
- *                             at a time. One right-hand side per
+ *                             at a time, one right-hand side per
  *                             work-group. Resolved to 5 (and so on; mode 1
  *                             for d = 3) where not supported.
  *                             Default 1; the row sweep wins with many

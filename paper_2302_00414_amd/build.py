@@ -39,12 +39,13 @@ DEVICE_FLAGS = [
 ]
 
 
-# Per-file additions. The matrix-core register tile clears single
+# Per-file additions. The matrix-core register tiles clear single
 # accumulator elements between operations, and the matrix-core window sums
 # use every accumulator in vector code after a few operations; with the
 # accumulators in ordinary VGPRs neither needs a round trip through AGPRs.
 FILE_FLAGS = {
     "interp_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "spread_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "spread_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
@@ -66,7 +67,7 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:

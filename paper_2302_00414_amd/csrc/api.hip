@@ -13,6 +13,7 @@
 #include <numeric>
 #include <string>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/nfft.h"
@@ -45,6 +46,34 @@ int default_tuning(int knob, int d) {
     case NFFT_TUNE_SPREAD_MODE: return env_int("NFFT_SPREAD_MODE", 1);
     default: return 0;
   }
+}
+
+// The knobs that ask for the LDS kernel of spread mode 1: the mode itself, its
+// threads and its tile layout. A plan with none of them set, in the tuning or
+// in the environment, leaves the kernel of the default mode to the library.
+const std::pair<int, const char*> kSpreadKnobs[] = {
+    {NFFT_TUNE_SPREAD_MODE, "NFFT_SPREAD_MODE"},
+    {NFFT_TUNE_SPREAD_THREADS, "NFFT_SPREAD_THREADS"},
+    {NFFT_TUNE_SPREAD_PLANES, "NFFT_SPREAD_PLANES"}};
+
+unsigned asked_knobs(const int* tuning, int ntuning) {
+  unsigned m = 0;
+  for (const auto& k : kSpreadKnobs)
+    if ((tuning && k.first < ntuning && tuning[k.first]) || env_int(k.second, 0))
+      m |= 1u << k.first;
+  return m;
+}
+
+// Whether the work-item size is left to the library (neither an entry of the
+// tuning array nor the environment sets it). The matrix-core form of spread
+// mode 1 then takes up to two of the default items of a tile as one: fewer
+// tiles to sum afterwards (linogram of 2097152 nodes, M = 512, m = 8, float64:
+// 320 -> 253 us; polar set of 262144 nodes, M = 256, m = 6, float32: 36.0 ->
+// 32.9 us; 4096 nodes at M = 32, where no tile is split any more: 20.9 ->
+// 18.8 us; never slower in the sets measured, while 1024 nodes an item are).
+bool default_items(const int* tuning, int ntuning) {
+  const int v = tuning && NFFT_TUNE_ITEM_NODES < ntuning ? tuning[NFFT_TUNE_ITEM_NODES] : 0;
+  return v == 0 && env_int("NFFT_ITEM_NODES", 0) == 0;
 }
 
 thread_local std::string g_noplan_error;
@@ -100,6 +129,8 @@ struct nfft_plan_s {
   Geom g{};
   int maxpop = 0;
   int tune[NFFT_TUNE_COUNT] = {0};   // resolved tuning
+  unsigned asked = 0;                // bits of kSpreadKnobs set by the caller (see picks_kernel)
+  int item_cut = 0;                  // most nodes of a spreading work item of this plan
   int64_t bytes = 0;                 // workspace bytes owned by this handle
   std::shared_ptr<SharedData> shared; // node data, weights and tables
   std::string last_error;
@@ -248,7 +279,7 @@ int resolve_tuning(int d, int Ms, int m, int precision, const int* in, int n, in
   // the matrix-core register tile: d = 2, tile edge 16, 2m + 1 <= 16, or
   // d = 3, tile edge 8, 2m <= 8 (float32 or float64); elsewhere the vector
   // register tile (and its own fallback)
-  if (mode == 7 && !nfft::spread_mma_supported(d, T, precision == NFFT_F64, m) &&
+  if (mode == 7 && !(nfft::spread_tile_supported(d, T, m) && 2 * m + 1 <= 16) &&
       !nfft::spread3_mma_supported(d, T, precision == NFFT_F64, m))
     mode = 5;
   // the grid-tile gather: float32, d = 2, tile edge 16, m <= 8; elsewhere
@@ -268,7 +299,7 @@ int resolve_tuning(int d, int Ms, int m, int precision, const int* in, int n, in
   const bool f64 = precision == NFFT_F64;
   const size_t one = mode == 6   ? nfft::spread_gather_lds_bytes(m)
                      : mode == 7 && d == 3 ? nfft::spread3_mma_lds_bytes(f64)
-                     : mode == 7 ? nfft::spread_mma_lds_bytes(m, nt, precision == NFFT_F64)
+                     : mode == 7 ? std::max(f64 ? 0 : nfft::spread_mma_lds_bytes(m, nt), nfft::spread_tile_lds_bytes(m, f64))
                      : mode == 5 ? nfft::spread_reg_lds_bytes(m)
                                  : nfft::spread_lds_bytes(d, f64, m, T, Ptot, nt, 1, planes);
   const size_t multi = out[NFFT_TUNE_RHS_PER_GROUP] > 1
@@ -700,7 +731,7 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   // tile starts and work items (at most kItem nodes of one tile each)
   std::vector<int32_t> hstart(g.nbins + 1);
   std::vector<int32_t> istart, icount, ibin, ifirst(g.nbins + 1);  // ifirst: items of tile b
-  const int kItem = p->tune[NFFT_TUNE_ITEM_NODES];
+  const int kItem = p->item_cut;
   int64_t acc = 0;
   p->maxpop = 0;
   for (int b = 0; b < g.nbins; ++b) {
@@ -732,48 +763,29 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
     if (hc[b] == 0) ebins.push_back(b);
   p->nempty = (int)ebins.size();
   g.nsub = (int)istart.size();
-  // work items of the forward's window sums: runs of whole groups of 16
-  // nodes, at most kInterpItem, of one tile. In tile order, an eighth of them
-  // for each XCD (work-group i runs on XCD i mod 8): neighbouring tiles read
-  // the same grid lines through one L2.
-  std::vector<int32_t> fitem;
-  if (nfft::interp_mma_supported(d, g.T, p->prec == NFFT_F64, p->m)) {
-    std::vector<int32_t> it;
-    for (int b = 0; b < g.nbins; ++b) {
-      const int n = hc[b], k = (n + nfft::kInterpItem - 1) / nfft::kInterpItem;
-      for (int j = 0, s0 = 0; j < k; ++j) {
-        const int left = (n - s0 + 15) / 16;  // groups
-        const int c = std::min(n - s0, (left + k - j - 1) / (k - j) * 16);
-        it.insert(it.end(), {hstart[b] + s0, c, b, 0});
-        s0 += c;
-      }
-    }
-    const int n = (int)(it.size() / 4), per = (n + 7) / 8;
-    p->nfwd = 8 * per;
-    fitem.assign((size_t)4 * p->nfwd, 0);
-    for (int i = 0; i < n; ++i)
-      std::copy(it.begin() + 4 * i, it.begin() + 4 * i + 4,
-                fitem.begin() + 4 * ((i % per) * 8 + i / per));
-  }
-  // launch order: largest work items first, so that the work-groups that
+  // launch order of work items: largest first, so that the work-groups that
   // start last are the small remainders of tiles, in blocks of one item per
   // compute unit whose direction alternates: the first work-groups go one
   // to each compute unit, so that unit c receives the items of rank c,
   // 2C - 1 - c, 2C + c, ... (C compute units), large ones paired with small
   // ones (every item writes its own tile or slot, so the order changes no
   // result)
-  {
-    std::vector<int32_t> order(istart.size());
+  int ncu = 0;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess ||
+      ncu < 1)
+    ncu = 256;
+  auto launch_order = [&](const std::vector<int32_t>& count) {
+    std::vector<int32_t> order(count.size());
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t u, int32_t v) { return icount[u] > icount[v]; });
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess ||
-        ncu < 1)
-      ncu = 256;
+                     [&](int32_t u, int32_t v) { return count[u] > count[v]; });
     const size_t C = (size_t)ncu;
     for (size_t b0 = C; b0 < order.size(); b0 += 2 * C)
       std::reverse(order.begin() + b0, order.begin() + std::min(order.size(), b0 + C));
+    return order;
+  };
+  {
+    const std::vector<int32_t> order = launch_order(icount);
     auto permute = [&](std::vector<int32_t>& a) {
       std::vector<int32_t> t(a.size());
       for (size_t i = 0; i < a.size(); ++i) t[i] = a[order[i]];
@@ -784,6 +796,36 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
     permute(ibin);
     permute(islot);
   }
+  // work items of the forward's window sums, [n][4]: first node, nodes, tile.
+  // Matrix-core form: runs of whole groups of 16 nodes, at most kInterpItem,
+  // in tile order, an eighth of them for each XCD (work-group i runs on XCD
+  // i mod 8): neighbouring tiles read the same grid lines through one L2.
+  // Else runs of at most item_nodes nodes in the launch order above.
+  std::vector<int32_t> fitem;
+  {
+    const bool mma = nfft::interp_mma_supported(d, g.T, p->prec == NFFT_F64, p->m);
+    const int K = mma ? nfft::kInterpItem : p->tune[NFFT_TUNE_ITEM_NODES];
+    std::vector<int32_t> it, ic;
+    for (int b = 0; b < g.nbins; ++b) {
+      const int n = hc[b], k = (n + K - 1) / K;
+      for (int j = 0, s0 = 0; j < k; ++j) {
+        const int groups = (n - s0 + 15) / 16;
+        const int c = mma ? std::min(n - s0, (groups + k - j - 1) / (k - j) * 16) : std::min(K, n - s0);
+        it.insert(it.end(), {hstart[b] + s0, c, b, 0});
+        ic.push_back(c);
+        s0 += c;
+      }
+    }
+    const int n = (int)ic.size(), per = (n + 7) / 8;
+    p->nfwd = mma ? 8 * per : n;
+    fitem.assign((size_t)4 * p->nfwd, 0);
+    std::vector<int32_t> order;
+    if (!mma) order = launch_order(ic);
+    for (int i = 0; i < n; ++i) {
+      const int from = mma ? i : order[i], to = mma ? (i % per) * 8 + i / per : i;
+      std::copy(it.begin() + 4 * from, it.begin() + 4 * from + 4, fitem.begin() + 4 * to);
+    }
+  }
   HIP_TRY(p, hipMemcpyAsync(bstart, hstart.data(), (g.nbins + 1) * sizeof(int32_t),
                             hipMemcpyHostToDevice, s));
   p->shared->hbin_start = hstart;
@@ -792,9 +834,15 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
                                (int32_t*)chunk_count, s));
   HIP_TRY(p, nfft::launch_chunk_offsets((const int32_t*)chunk_count, (const int32_t*)bstart,
                                         nchunks, g.nbins, (int32_t*)offsets, s));
-  TRY(dalloc(p, &p->perm, N * sizeof(int32_t)));
-  TRY(dalloc(p, &p->loc, N * sizeof(uint32_t)));
-  TRY(dalloc(p, &p->frac, N * d * sizeof(R)));
+  // kNodePad entries past the last node, zero: the matrix-core spreading reads
+  // whole chunks of nodes
+  constexpr size_t pad = nfft::kNodePad;
+  TRY(dalloc(p, &p->perm, (N + pad) * sizeof(int32_t)));
+  TRY(dalloc(p, &p->loc, (N + pad) * sizeof(uint32_t)));
+  TRY(dalloc(p, &p->frac, (N * d + pad) * sizeof(R)));
+  HIP_TRY(p, hipMemsetAsync(p->perm + N, 0, pad * sizeof(int32_t), s));
+  HIP_TRY(p, hipMemsetAsync(p->loc + N, 0, pad * sizeof(uint32_t), s));
+  HIP_TRY(p, hipMemsetAsync((R*)p->frac + N * d, 0, pad * sizeof(R), s));
   HIP_TRY(p, nfft::launch_scatter<R>((const int32_t*)bin, (const int32_t*)rank,
                                      (const int32_t*)offsets, (const uint32_t*)loc_u,
                                      (const double*)frac_u, N, d, g.nbins, p->perm, p->loc,
@@ -839,7 +887,8 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
     TRY(dalloc(p, &p->fwd_items, fitem.size() * sizeof(int32_t)));
     HIP_TRY(p, hipMemcpyAsync(p->fwd_items, fitem.data(), fitem.size() * 4, hipMemcpyHostToDevice, s));
   }
-  TRY(dalloc(p, &p->w, N * sizeof(cplx<R>)));
+  TRY(dalloc(p, &p->w, (N + pad) * sizeof(cplx<R>)));
+  HIP_TRY(p, hipMemsetAsync((cplx<R>*)p->w + N, 0, pad * sizeof(cplx<R>), s));
   TRY(alloc_workspace<R>(p, s));
   TRY(build_tables<R>(p));
   if (uses_psi(p->tune[NFFT_TUNE_SPREAD_MODE])) TRY(ensure_psi<R>(p, s));
@@ -928,6 +977,7 @@ int run_adjoint(nfft_plan_t p, const void* f, void* fhat, int nrhs, hipStream_t 
   sa.nr = nrhs > 1 ? p->tune[NFFT_TUNE_RHS_PER_GROUP] : 1;
   sa.planes = p->tune[NFFT_TUNE_SPREAD_PLANES];
   sa.mode = p->tune[NFFT_TUNE_SPREAD_MODE];
+  sa.pick = p->asked == 0;
   sa.psi = uses_psi(sa.mode) ? (const R*)p->shared->psi : nullptr;
   if constexpr (std::is_same<R, float>::value) {
     if (sa.mode == 6) {
@@ -1118,9 +1168,6 @@ int run_forward(nfft_plan_t p, const void* fhat, void* f, int nrhs, hipStream_t 
   ia.grid = (const cplx<R>*)p->grid;
   ia.f = (cplx<R>*)f;
   ia.sub = (const cplx<R>*)sub;
-  ia.item_start = p->item_start;
-  ia.item_count = p->item_count;
-  ia.item_bin = p->item_bin;
   ia.items = p->fwd_items;
   ia.nitems = p->nfwd;
   ia.coef = (const R*)p->coef;
@@ -1315,6 +1362,7 @@ int64_t nfft_footprint(int d, int M, double sigma, int m, int64_t N, int precisi
   const int64_t R_ = max_rhs;
   int64_t bytes = 0;
   bytes += N * 4 + N * 4 + N * d * rb;                     // perm, loc, frac
+  bytes += nfft::kNodePad * (4 + 4 + rb + cb);            // their padding and the weights'
   bytes += std::max<int64_t>(1, nsub_max) * 4 * 3 + (nbins + 1) * 4 + nbins * 4;  // item tables
   bytes += N * cb;                                        // weights
   bytes += R_ * (nbins + nsub_max) * Ptot * cb;           // tile and item partials
@@ -1324,8 +1372,7 @@ int64_t nfft_footprint(int d, int M, double sigma, int m, int64_t N, int precisi
   bytes += R_ * ipow(Ms, d) * cb;                         // forward grid
   bytes += M * 8 + Ms * cb;                               // tables
   if (d == 2) bytes += N * 4 * m * rb;                    // window factors (spread mode 3)
-  if (nfft::interp_mma_supported(d, T, precision == NFFT_F64, m))
-    bytes += (nbins + N / nfft::kInterpItem + 8) * 16;    // forward work items
+  bytes += (nbins + N / std::min(K, nfft::kInterpItem) + 8) * 16;  // forward work items
   return bytes;
 }
 
@@ -1358,6 +1405,7 @@ int nfft_plan_tuned(nfft_plan_t* out, int d, int M, double sigma, int m, int64_t
   p->Ms = oversampled(M, sigma);
   p->b = M_PI * (2.0 - 1.0 / sigma);
   std::copy(tune, tune + NFFT_TUNE_COUNT, p->tune);
+  p->item_cut = tune[NFFT_TUNE_ITEM_NODES];
   Geom& g = p->g;
   g.d = d;
   g.Ms = p->Ms;
@@ -1373,6 +1421,10 @@ int nfft_plan_tuned(nfft_plan_t* out, int d, int M, double sigma, int m, int64_t
   g.Ms_shift = 0;
   while ((1 << g.Ms_shift) < g.Ms) ++g.Ms_shift;
   g.N = N;
+  p->asked = asked_knobs(tuning, ntuning);
+  if (default_items(tuning, ntuning) && !p->asked &&
+      nfft::spread_tile_preferred(d, g.T, precision == NFFT_F64, m, N, g.nbins))
+    p->item_cut *= 2;
   if (hipGetDevice(&p->device) != hipSuccess) {
     free_plan(p);
     return fail(nullptr, NFFT_EDEVICE, "no HIP device available");
@@ -1463,11 +1515,12 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
     planes = {1, 2};
   }
   if (d <= 2 && nrhs > 1) rpg = {1, 2, 4, 8};
-  // float64: the work-group size matters to the matrix-core register tile only
-  if (d == 2 && !f32) threads = {128, 256};
   if (d == 2) modes = {1, 2, 3, 4, 7};
   if (d == 2 && f32) modes = {1, 2, 3, 4, 5, 7};
   if (d == 3) modes = {1, 7};
+  // the tile shape of mode 7 at m = 8 (where mode 7 itself is not defined) as the
+  // default mode's choice
+  if (d == 2 && m == 8) modes.push_back(0);
   // the grid-tile gather holds 32 right-hand sides in the lanes of a wave;
   // its units also try 768 list entries (fewer split tiles than 512, fewer
   // long units than 1024)
@@ -1479,6 +1532,7 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
   nfft_plan_t best = nullptr;
   double best_t = -1.0;
   int best_tune[NFFT_TUNE_COUNT] = {0};
+  unsigned best_asked = 0;
   for (int T : tiles) {
     if (T > Ms) continue;
     for (int K : items) {
@@ -1521,11 +1575,14 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
             // the register-tile kernels (modes 5, 7) take one rhs per work-group
             // and no LDS tile layout
             if ((md == 5 || md == 7) && (nr > 1 || pl != planes[0])) continue;
+            // the library's own choice has one shape; mode 7 for d = 2 has the
+            // tile shape (64 and 128 threads, any thread count in float64) and in
+            // float32 two more
+            if (md == 0 && (nr > 1 || nt != threads[0] || pl != planes[0])) continue;
+            if (md == 7 && d == 2 && nt != threads[0] && (!f32 || nt == 128)) continue;
             // the gather (mode 6) has one shape; 768 entries per unit are for it alone
             if (md == 6 && (nr > 1 || pl != planes[0] || nt != threads[0])) continue;
             if (K == 768 && md != 6) continue;
-            // float64: only mode 7 takes the thread count
-            if (!f32 && md != 7 && nt != threads[0]) continue;
             if (nt == 512 && md < 5) continue;
             if (nr > 2 && md == 2) continue;  // the row sweep takes at most two rhs per wave
             if (uses_psi(md) && !have_psi) continue;
@@ -1536,11 +1593,13 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
             if (resolve_tuning(d, Ms, m, precision, in, NFFT_TUNE_COUNT, res, nullptr) != NFFT_OK)
               continue;
             std::copy(res, res + NFFT_TUNE_COUNT, p->tune);
+            p->asked = md == 0 && d == 2 ? 0 : 1u << NFFT_TUNE_SPREAD_MODE;
             const double t = time_adjoint(p, f, fhat, nrhs, s);
             if (t < 0) continue;
             if (best_t < 0 || t < best_t) {
               best_t = t;
               std::copy(res, res + NFFT_TUNE_COUNT, best_tune);
+              best_asked = p->asked;
               if (best && best != p) free_plan(best);
               best = p;
               mine = true;
@@ -1548,6 +1607,7 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
           }
       if (mine) {
         std::copy(best_tune, best_tune + NFFT_TUNE_COUNT, p->tune);
+        p->asked = best_asked;
       } else {
         free_plan(p);
       }
@@ -1961,6 +2021,9 @@ int nfft_set_tuning(nfft_plan_t p, int knob, int value) {
     HIP_TRY(p, hipStreamSynchronize(nullptr));
   }
   std::copy(out, out + NFFT_TUNE_COUNT, p->tune);
+  for (const auto& k : kSpreadKnobs)
+    if (k.first == knob)
+      p->asked = value || env_int(k.second, 0) ? p->asked | 1u << knob : p->asked & ~(1u << knob);
   return NFFT_OK;
 }
 

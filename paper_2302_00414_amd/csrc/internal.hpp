@@ -40,6 +40,10 @@ template <typename R>
 hipError_t launch_zero_tiles(cplx<R>* tilep, int64_t tile_rs, const int32_t* bins, int nbins,
                              int Ptot, int nrhs, hipStream_t s);
 
+// Entries past the last node of the plan's node arrays (cell words, offsets,
+// weights, indices), zero.
+constexpr int64_t kNodePad = 256;
+
 // ------------------------------------------------------- spreading / sums
 // Tile partials: every tile owns a padded-tile slot in `tilep` ([rhs][tile]
 // [P^d], zero for tiles without nodes). A tile with a single work item is
@@ -73,6 +77,7 @@ struct SpreadArgs {
                              //   (float32; see launch_spread_gather),
                              // 7 padded tile on the matrix cores (d = 2, 3;
                              //   float32 and float64)
+  bool pick;                 // mode 1 by default: the kernel is the library's choice
   const R* psi;              // d = 2: window factors [N][2m][2] in tile order (mode 3)
 };
 template <typename R>
@@ -125,13 +130,21 @@ hipError_t launch_psi(const R* frac, int64_t N, int m, const R* coef, R* psi, hi
 bool spread_reg_supported(int d, int T, bool f64);
 size_t spread_reg_lds_bytes(int m);
 hipError_t launch_spread_reg(const SpreadArgs<float>& a, int nrhs, hipStream_t s);
-// Padded tile on the matrix cores, one tile row of nodes at a time (float32
-// or float64, d = 2, tile edge 16, 2m + 1 <= 16, nodes row-sorted within
-// tiles).
+// Padded tile on the matrix cores, one tile row of nodes at a time, every wave
+// a padded tile of its own (float32, d = 2, tile edge 16, 2m + 1 <= 16, nodes
+// row-sorted within tiles): mode 7 with 256 or 512 threads.
 bool spread_mma_supported(int d, int T, bool f64, int m);
-size_t spread_mma_lds_bytes(int m, int nt, bool f64);
+size_t spread_mma_lds_bytes(int m, int nt);
+hipError_t launch_spread_mma(const SpreadArgs<float>& a, int nrhs, hipStream_t s);
+// One padded tile per work-group on the matrix cores (float32 or float64, d =
+// 2, tile edge 16, m <= 8, nodes row-sorted within tiles): mode 7 (m <= 7) in
+// float64, with 64 or 128 threads or for several right-hand sides, and the
+// default mode where spread_tile_preferred says so.
+bool spread_tile_supported(int d, int T, int m);
+bool spread_tile_preferred(int d, int T, bool f64, int m, int64_t N, int64_t ntiles);
+size_t spread_tile_lds_bytes(int m, bool f64);
 template <typename R>
-hipError_t launch_spread_mma(const SpreadArgs<R>& a, int nrhs, hipStream_t s);
+hipError_t launch_spread_tile(const SpreadArgs<R>& a, int nrhs, hipStream_t s);
 // The d = 3 form of mode 7: one wave holds the padded tile (tile edge 8,
 // 2m <= 8, nodes sorted by their dimension-0 cell within tiles) in
 // matrix-core accumulators, float32 or float64.
@@ -169,10 +182,7 @@ struct InterpArgs {
   const cplx<R>* grid;       // full oversampled grid, C order, rhs stride grid_rs
   cplx<R>* f;                // output samples, caller order, rhs stride f_rs
   const cplx<R>* sub;        // if set: f = sub - (window sums), sub in caller order, stride f_rs
-  const int32_t* item_start;
-  const int32_t* item_count;
-  const int32_t* item_bin;
-  const int32_t* items;      // matrix-core form: [nitems][4] first node, nodes (0: padding), tile, 0
+  const int32_t* items;      // [nitems][4] first node, nodes (0: padding), tile, 0
   int nitems;
   const R* coef;
   const R* psi;              // d = 2: window factor table [N][2m][2] in tile order, or null

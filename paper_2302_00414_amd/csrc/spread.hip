@@ -344,7 +344,7 @@ template <typename R, int D, int MW>
 __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   extern __shared__ unsigned char smem_raw[];
   cplx<R>* tile = reinterpret_cast<cplx<R>*>(smem_raw);
-  const int item = blockIdx.x;
+  const int4 it = reinterpret_cast<const int4*>(a.items)[blockIdx.x];
   const int rhs = blockIdx.y;
   const int P = a.g.P;
   const int Ptot = a.g.Ptot;
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   // tile origin (in cells) of this work item's tile, per dimension
   int org[3] = {0, 0, 0};
   {
-    int bb = a.item_bin[item];
+    int bb = it.z;
     for (int t = D - 1; t >= 0; --t) {
       org[t] = (bb % nb) * a.g.T - a.g.m;
       bb /= nb;
@@ -393,8 +393,7 @@ __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   __syncthreads();
 
   const int64_t N = a.g.N;
-  const int start = a.item_start[item];
-  const int cnt = a.item_count[item];
+  const int start = it.x, cnt = it.y;
   cplx<R>* f = a.f + rhs * a.f_rs;
   for (int k = threadIdx.x; k < cnt; k += blockDim.x) {
     const int i = start + k;
@@ -470,7 +469,7 @@ template <typename R, int D, int MW>
 static hipError_t interp_dm(const InterpArgs<R>& a, int nrhs, hipStream_t s) {
   size_t lds = (size_t)a.g.Ptot * sizeof(cplx<R>) +
                (std::is_same<R, double>::value ? 2 * MW * (PolyDeg<R>::value + 1) * sizeof(R) : 0);
-  hipLaunchKernelGGL((interp_kernel<R, D, MW>), dim3(a.g.nsub, nrhs), dim3(256), lds, s, a);
+  hipLaunchKernelGGL((interp_kernel<R, D, MW>), dim3(a.nitems, nrhs), dim3(256), lds, s, a);
   return hipGetLastError();
 }
 
@@ -510,8 +509,17 @@ hipError_t launch_spread(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
   if (a.g.nsub == 0) return hipSuccess;
   if (a.mode == 2 && spread_rows_supported(a.g.d, a.g.P)) return launch_spread_rows<R>(a, nrhs, s);
   if (a.nr > 1 && a.g.d <= 2) return launch_spread_multi<R>(a, nrhs, s);
-  if (a.mode == 7 && spread_mma_supported(a.g.d, a.g.T, !std::is_same<R, float>::value, a.g.m))
-    return launch_spread_mma<R>(a, nrhs, s);
+  constexpr bool f64 = !std::is_same<R, float>::value;
+  if (a.mode == 7 && spread_tile_supported(a.g.d, a.g.T, a.g.m)) {
+    // float32 and one right-hand side: the thread count selects the shape (the
+    // faster one depends on how the nodes fill the tiles; the autotuner tries
+    // both)
+    if constexpr (!f64)
+      if (nrhs == 1 && a.nt >= 256) return launch_spread_mma(a, nrhs, s);
+    return launch_spread_tile<R>(a, nrhs, s);
+  }
+  if (a.mode == 1 && a.pick && spread_tile_preferred(a.g.d, a.g.T, f64, a.g.m, a.g.N, a.g.nbins))
+    return launch_spread_tile<R>(a, nrhs, s);
   if (a.mode == 7 && spread3_mma_supported(a.g.d, a.g.T, !std::is_same<R, float>::value, a.g.m))
     return launch_spread3_mma<R>(a, nrhs, s);
   if constexpr (std::is_same<R, float>::value) {
@@ -530,7 +538,7 @@ hipError_t launch_spread(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
 
 template <typename R>
 hipError_t launch_interp(const InterpArgs<R>& a, int nrhs, hipStream_t s) {
-  if (a.g.nsub == 0) return hipSuccess;
+  if (a.nitems == 0) return hipSuccess;
   if constexpr (std::is_same<R, float>::value) {
     if (interp_mma_supported(a.g.d, a.g.T, false, a.g.m)) return launch_interp_mma(a, nrhs, s);
   }

@@ -1,5 +1,5 @@
-// Spreading for d = 2 on the matrix cores (float32 and float64), the nodes
-// of a work item taken one tile row at a time (Algorithm 2.4 step 1 with the
+// Spreading for d = 2 on the matrix cores (float32), the nodes of a work item
+// taken one tile row at a time (Algorithm 2.4 step 1 with the
 // weights of (3.7)).
 //
 // A node in tile row r (tile-local cell (r, l1)) reaches the padded rows
@@ -9,7 +9,7 @@
 // therefore update a block of 16 rows x 32 padded columns,
 //     G[i][c] += sum_n A_n[i] B_n[c] c_n,
 // a product whose inner dimension runs over the nodes. v_mfma_f32_16x16x4f32
-// (v_mfma_f64_16x16x4f64 in float64) takes four nodes at a time: lane (k, i) supplies A_k[i] (row factor times
+// takes four nodes at a time: lane (k, i) supplies A_k[i] (row factor times
 // the real or the imaginary part of c_k = w_k f_k) and B_k[i] (column
 // factor), and four operations per four nodes cover the two column blocks
 // (padded columns 0..15 and 16..31) times the real and imaginary parts.
@@ -31,13 +31,11 @@ namespace nfft {
 
 namespace {
 
-// Per precision: the accumulator block of v_mfma_*_16x16x4 (four elements a
-// lane, column l & 15 of the 16 x 16 block; row 4 (l >> 4) + v for element v
-// of lane l in float32, row 4 v + (l >> 4) in float64), the operation, and a
-// lane read.
+// The accumulator block of v_mfma_f32_16x16x4 (four elements a lane, column
+// l & 15 of the 16 x 16 block, row 4 (l >> 4) + v for element v of lane l),
+// the operation, and a lane read.
 template <typename R> struct MmaT;
 template <> struct MmaT<float> {
-  static constexpr bool kRowsByQuarter = true;  // row 4 (l >> 4) + v
   typedef float v4 __attribute__((ext_vector_type(4)));
   static __device__ __forceinline__ v4 mfma(float a, float b, v4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -46,20 +44,6 @@ template <> struct MmaT<float> {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_addr, __float_as_int(v)));
   }
 };
-template <> struct MmaT<double> {
-  static constexpr bool kRowsByQuarter = false;  // row 4 v + (l >> 4)
-  typedef double v4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ v4 mfma(double a, double b, v4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ double read(double v, int byte_addr) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_ds_bpermute(byte_addr, (int)(u & 0xffffffffLL));
-    const int hi = __builtin_amdgcn_ds_bpermute(byte_addr, (int)(u >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-  }
-};
-
 // y0, y1, Re c, Im c of a staged node
 template <typename R> struct alignas(4 * sizeof(R)) MmaNode {
   R y0, y1, cx, cy;
@@ -94,7 +78,6 @@ __global__ __launch_bounds__(64 * NW) void spread_mma_kernel(SpreadArgs<R> a) {
   constexpr int NB = kMmaBatch;
   constexpr int DEG = PolyDeg<R>::value;
   typedef typename MmaT<R>::v4 v4;
-  constexpr bool QR = MmaT<R>::kRowsByQuarter;
   static_assert(K2 + 1 <= 16, "the rows of one tile row's nodes fit in 16 slots");
   static_assert((P * P) % 2 == 0 && P % 2 == 0, "tiles are summed two cells at a time");
   extern __shared__ double lds_d[];
@@ -206,10 +189,9 @@ __global__ __launch_bounds__(64 * NW) void spread_mma_kernel(SpreadArgs<R> a) {
       }
       gbase += ng;
       // padded row r is complete for this wave: slot r (accumulator element
-      // v of lane l is slot 4 (l >> 4) + v in float32, 4 v + (l >> 4) in
-      // float64; column l & 15 of its block)
-      constexpr int v = QR ? (r & 3) : (r >> 2);
-      const bool done = kq == (QR ? (r >> 2) : (r & 3));
+      // v of lane l is slot 4 (l >> 4) + v; column l & 15 of its block)
+      constexpr int v = r & 3;
+      const bool done = kq == (r >> 2);
       cplx<R> lo = mkc<R>(acc0r[v], acc0i[v]);
       cplx<R> hi = mkc<R>(acc1r[v], acc1i[v]);
       if (done) {
@@ -237,7 +219,7 @@ __global__ __launch_bounds__(64 * NW) void spread_mma_kernel(SpreadArgs<R> a) {
     // padded rows 16 .. P-1: slot s holds padded row 16 + s
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int row = 16 + (QR ? 4 * kq + v : 4 * v + kq);
+      const int row = 16 + 4 * kq + v;
       if (row < P) {
         cplx<R>* rowp = mine + row * P;
         cplx<R> lo = mkc<R>(acc0r[v], acc0i[v]);
@@ -263,52 +245,37 @@ __global__ __launch_bounds__(64 * NW) void spread_mma_kernel(SpreadArgs<R> a) {
   }
 
   // the waves' tiles summed in wave order: a fixed order, so the result does
-  // not depend on timing (float32: two cells at a time)
+  // not depend on timing; two cells at a time
   __syncthreads();
   const int slot = a.item_slot[item];
   cplx<R>* out = slot < 0 ? a.tilep + rhs * a.tile_rs + (int64_t)a.item_bin[item] * (P * P)
                           : a.itemp + rhs * a.item_rs + (int64_t)slot * (P * P);
-  if constexpr (std::is_same<R, float>::value) {
-    const float4* t4 = reinterpret_cast<const float4*>(tiles);
-    float4* o4 = reinterpret_cast<float4*>(out);
-    for (int i = tid; i < P * P / 2; i += NT) {
-      float4 s = t4[i];
+  const float4* t4 = reinterpret_cast<const float4*>(tiles);
+  float4* o4 = reinterpret_cast<float4*>(out);
+  for (int i = tid; i < P * P / 2; i += NT) {
+    float4 s = t4[i];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) {
-        const float4 u = t4[w * (P * P / 2) + i];
-        s.x += u.x;
-        s.y += u.y;
-        s.z += u.z;
-        s.w += u.w;
-      }
-      o4[i] = s;
+    for (int w = 1; w < NW; ++w) {
+      const float4 u = t4[w * (P * P / 2) + i];
+      s.x += u.x;
+      s.y += u.y;
+      s.z += u.z;
+      s.w += u.w;
     }
-  } else {
-    for (int i = tid; i < P * P; i += NT) {
-      cplx<R> s = tiles[i];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) {
-        const cplx<R> u = tiles[w * (P * P) + i];
-        s.x += u.x;
-        s.y += u.y;
-      }
-      out[i] = s;
-    }
+    o4[i] = s;
   }
 }
 
 bool spread_mma_supported(int d, int T, bool f64, int m) {
-  (void)f64;  // float32 and float64
-  return d == 2 && T == 16 && m >= 1 && 2 * m + 1 <= 16;
+  return d == 2 && T == 16 && !f64 && m >= 1 && 2 * m + 1 <= 16;
 }
 
-// 64 or 128 threads: two waves; 256: four; 512: eight
-static int mma_waves(int nt) { return nt >= 512 ? 8 : nt >= 256 ? 4 : 2; }
+// 256 threads: four waves; 512: eight
+static int mma_waves(int nt) { return nt >= 512 ? 8 : 4; }
 
 template <typename R, int MW>
 static size_t mma_lds_m(int nw) {
-  return nw == 8 ? MmaLds<R, MW, 8>::bytes
-                 : nw == 4 ? MmaLds<R, MW, 4>::bytes : MmaLds<R, MW, 2>::bytes;
+  return nw == 8 ? MmaLds<R, MW, 8>::bytes : MmaLds<R, MW, 4>::bytes;
 }
 
 template <typename R>
@@ -325,10 +292,7 @@ static size_t mma_lds(int m, int nw) {
   }
 }
 
-size_t spread_mma_lds_bytes(int m, int nt, bool f64) {
-  const int nw = mma_waves(nt);
-  return f64 ? mma_lds<double>(m, nw) : mma_lds<float>(m, nw);
-}
+size_t spread_mma_lds_bytes(int m, int nt) { return mma_lds<float>(m, mma_waves(nt)); }
 
 template <typename R, int MW>
 static hipError_t spread_mma_m(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
@@ -337,18 +301,15 @@ static hipError_t spread_mma_m(const SpreadArgs<R>& a, int nrhs, hipStream_t s) 
   if (nw == 8)
     hipLaunchKernelGGL((spread_mma_kernel<R, MW, 8>), grid, dim3(512), (MmaLds<R, MW, 8>::bytes),
                        s, a);
-  else if (nw == 4)
-    hipLaunchKernelGGL((spread_mma_kernel<R, MW, 4>), grid, dim3(256), (MmaLds<R, MW, 4>::bytes),
-                       s, a);
   else
-    hipLaunchKernelGGL((spread_mma_kernel<R, MW, 2>), grid, dim3(128), (MmaLds<R, MW, 2>::bytes),
+    hipLaunchKernelGGL((spread_mma_kernel<R, MW, 4>), grid, dim3(256), (MmaLds<R, MW, 4>::bytes),
                        s, a);
   return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_spread_mma(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
-  if (!spread_mma_supported(a.g.d, a.g.T, !std::is_same<R, float>::value, a.g.m))
+hipError_t launch_spread_mma(const SpreadArgs<float>& a, int nrhs, hipStream_t s) {
+  using R = float;
+  if (!spread_mma_supported(a.g.d, a.g.T, false, a.g.m))
     return hipErrorInvalidValue;
   if (a.g.nsub == 0) return hipSuccess;
   switch (a.g.m) {
@@ -362,8 +323,5 @@ hipError_t launch_spread_mma(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
     default: return hipErrorInvalidValue;
   }
 }
-
-template hipError_t launch_spread_mma<float>(const SpreadArgs<float>&, int, hipStream_t);
-template hipError_t launch_spread_mma<double>(const SpreadArgs<double>&, int, hipStream_t);
 
 }  // namespace nfft

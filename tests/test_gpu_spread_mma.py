@@ -1,0 +1,77 @@
+"""The matrix-core spreading (d = 2, tile edge 16: mode 7 for m <= 7, mode 1
+where it is preferred) against the oracle NFFT, at the sizes where its cuts can
+go wrong: groups of four and chunks of 64 nodes that are not full, one node,
+tiles of several work items, empty tiles and bands, nodes on grid lines (closed
+edges; at m = 8 the row edge has its own sums), and right-hand sides that do
+not fill the last work-group.
+
+Tolerances (relative l2): float64 differs from the oracle by rounding only,
+1e-12; two float32 evaluations in different orders agree to 2e-6, and a float32
+transform differs from the oracle by rounding only, 2e-6.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import metrics, nfft as onfft
+from paper_2302_00414_amd import workloads as wl
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+TOL = {"f64": 1e-12, "f32": 2e-6}
+
+
+def _nodes(kind, Ms):
+    if kind == "one":
+        return np.array([[0.123, -0.4567]])
+    if kind == "sparse":
+        return wl.uniform_nodes(5 * (Ms // 16) ** 2 + 3, 2, 3)
+    if kind == "crowded":     # most nodes in one tile: several items, full chunks, a remainder
+        return np.concatenate([0.9 / Ms * wl.uniform_nodes(1100, 2, 4) * 16 + 8.0 / Ms,
+                               wl.uniform_nodes(70, 2, 5)])
+    if kind == "row":         # one row of cells: one band, every column
+        x = wl.uniform_nodes(519, 2, 6)
+        x[:, 0] = (3.0 + 0.9 * (x[:, 0] + 0.5)) / Ms
+        return x
+    x = wl.uniform_nodes(997, 2, 5)   # grid lines: rows, columns, both, and the wrap
+    x[::3, 0] = np.round(x[::3, 0] * Ms) / Ms
+    x[::5, 1] = np.round(x[::5, 1] * Ms) / Ms
+    x[0] = [-0.5, -0.5]
+    return x
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("kind,M,nrhs", [("one", 16, 1), ("sparse", 64, 2), ("crowded", 16, 5),
+                                         ("row", 16, 1), ("lines", 16, 3)])
+def test_spreading(prec, m, kind, M, nrhs):
+    from paper_2302_00414_amd.nfft import Plan
+    x = _nodes(kind, 2 * M)
+    N = x.shape[0]
+    print(f"[case] {kind} N={N} M={M} m={m} {prec} rhs={nrhs}", flush=True)
+    p = Plan(x, M, 2.0, m, precision=prec, max_rhs=nrhs, tuning={"spread_mode": 7 if m <= 7 else 1})
+    w = (1.0 + 0.5 * wl.complex_normal(N, 8)) / N
+    p.set_weights(w)
+    f = wl.complex_normal((nrhs, N), 9)
+    got = p.adjoint(torch.from_numpy(f).cuda()).cpu().numpy()
+    for r in range(nrhs):
+        want = onfft.adjoint(x, w * f[r], M, 2.0, m)
+        assert metrics.rel_err(got[r], want) <= TOL[prec], (kind, m, r)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("nrhs", [2, 7])
+def test_right_hand_sides_share_the_factors(prec, nrhs):
+    """Enough work-groups for several right-hand sides each: the same bits as
+    one at a time (every cell's sum has one order)."""
+    from paper_2302_00414_amd.nfft import Plan
+    M, m, N = 256, 6, 140003
+    x = wl.uniform_nodes(N, 2, 11)
+    p = Plan(x, M, 2.0, m, precision=prec, max_rhs=nrhs, tuning={"spread_mode": 7})
+    p.set_weights(np.full(N, 1.0 / N))
+    f = torch.from_numpy(wl.complex_normal((nrhs, N), 12)).to(p.cdtype).cuda()
+    both = p.adjoint(f)
+    one = torch.stack([p.adjoint(f[r]) for r in range(nrhs)])
+    rel = ((both - one).norm() / one.norm()).item()
+    assert rel <= {"f64": 1e-14, "f32": 1e-6}[prec], rel
