@@ -45,6 +45,7 @@ DEVICE_FLAGS = [
 # accumulators in ordinary VGPRs neither needs a round trip through AGPRs.
 FILE_FLAGS = {
     "interp_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "interp3_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "spread_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "spread_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }

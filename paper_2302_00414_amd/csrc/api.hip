@@ -803,7 +803,9 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   // Else runs of at most item_nodes nodes in the launch order above.
   std::vector<int32_t> fitem;
   {
-    const bool mma = nfft::interp_mma_supported(d, g.T, p->prec == NFFT_F64, p->m);
+    const bool f64 = p->prec == NFFT_F64;
+    const bool mma = nfft::interp_mma_supported(d, g.T, f64, p->m) ||
+                     nfft::interp3_mma_supported(d, g.T, f64, p->m);
     const int K = mma ? nfft::kInterpItem : p->tune[NFFT_TUNE_ITEM_NODES];
     std::vector<int32_t> it, ic;
     for (int b = 0; b < g.nbins; ++b) {

@@ -198,6 +198,9 @@ hipError_t launch_interp(const InterpArgs<R>& a, int nrhs, hipStream_t s);
 constexpr int kInterpItem = 256;  // most nodes of one of its work items
 bool interp_mma_supported(int d, int T, bool f64, int m);
 hipError_t launch_interp_mma(const InterpArgs<float>& a, int nrhs, hipStream_t s);
+// The d = 3 form (float32, tile edge 8, m = 4).
+bool interp3_mma_supported(int d, int T, bool f64, int m);
+hipError_t launch_interp3_mma(const InterpArgs<float>& a, int nrhs, hipStream_t s);
 
 // ------------------------------------------------------------------- FFT
 enum LoadMode { kLoadMerge = 0, kLoadLine = 1, kLoadPadScaled = 2 };

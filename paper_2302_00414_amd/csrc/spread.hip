@@ -541,6 +541,7 @@ hipError_t launch_interp(const InterpArgs<R>& a, int nrhs, hipStream_t s) {
   if (a.nitems == 0) return hipSuccess;
   if constexpr (std::is_same<R, float>::value) {
     if (interp_mma_supported(a.g.d, a.g.T, false, a.g.m)) return launch_interp_mma(a, nrhs, s);
+    if (interp3_mma_supported(a.g.d, a.g.T, false, a.g.m)) return launch_interp3_mma(a, nrhs, s);
   }
   switch (a.g.d) {
     case 1: NFFT_DISPATCH_M(interp_dm, R, 1, a, nrhs, s)

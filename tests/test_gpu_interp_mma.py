@@ -1,5 +1,5 @@
-"""The forward's window sums on the matrix cores (float32, d = 2, m >= 5)
-against the oracle NFFT, at the sizes where the kernel's cuts can go wrong:
+"""The forward's window sums on the matrix cores (float32; d = 2, m >= 5 and d =
+3, m = 4) against the oracle NFFT, at the sizes where the kernel's cuts can go wrong:
 groups of 16 nodes that are not full, one node, tiles of several work items,
 groups that span more rows than one block of 16 covers, nodes on grid lines
 (closed edges) on both axes, a grid of one tile, and right-hand sides that do
@@ -45,6 +45,35 @@ def test_window_sums(m, kind, M, nrhs):
     print(f"[case] {kind} N={x.shape[0]} M={M} m={m} rhs={nrhs}", flush=True)
     p = Plan(x, M, 2.0, m, precision="f32", max_rhs=nrhs)
     h = wl.complex_normal((nrhs, M * M), 7).astype(np.complex64)
+    got = p.forward(torch.from_numpy(h).cuda()).cpu().numpy()
+    for r in range(nrhs):
+        want = onfft.forward(x, h[r].astype(np.complex128), M, 2.0, m)
+        assert metrics.rel_err(got[r], want) <= TOL, (kind, m, r)
+
+
+def _nodes3(kind, Ms):
+    if kind == "one":
+        return np.array([[0.123, -0.4567, 0.31]])
+    if kind == "sparse":      # a few nodes per tile: groups span every plane
+        return wl.uniform_nodes(3 * (Ms // 8) ** 3 + 3, 3, 3)
+    if kind == "crowded":     # one tile of three work items and a remainder
+        return 0.9 * 8 / Ms * wl.uniform_nodes(2 * 256 + 37, 3, 4) + 4.0 / Ms
+    x = wl.uniform_nodes(701, 3, 5)   # grid planes of each dimension, and the wrap
+    for t in range(3):
+        x[t::4, t] = np.round(x[t::4, t] * Ms) / Ms
+    x[0] = [-0.5, -0.5, -0.5]
+    return x
+
+
+@pytest.mark.parametrize("m", [4])
+@pytest.mark.parametrize("kind,M,nrhs", [("one", 8, 1), ("sparse", 16, 2), ("crowded", 8, 1),
+                                         ("lines", 8, 3)])
+def test_window_sums_3d(m, kind, M, nrhs):
+    from paper_2302_00414_amd.nfft import Plan
+    x = _nodes3(kind, 2 * M)
+    print(f"[case] 3-D {kind} N={x.shape[0]} M={M} m={m} rhs={nrhs}", flush=True)
+    p = Plan(x, M, 2.0, m, precision="f32", max_rhs=nrhs)
+    h = wl.complex_normal((nrhs, M ** 3), 7).astype(np.complex64)
     got = p.forward(torch.from_numpy(h).cuda()).cpu().numpy()
     for r in range(nrhs):
         want = onfft.forward(x, h[r].astype(np.complex128), M, 2.0, m)
