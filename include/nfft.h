@@ -128,9 +128,8 @@ int nfft_plan(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t N,
  *   NFFT_TUNE_SPREAD_MODE     single right-hand-side spreading for d = 2:
  *                             1 = accumulation in LDS tiles (as the default,
  *                             with neither the mode nor the threads or planes
- *                             set: the kernel of mode 7, there up to m = 8,
- *                             where the nodes per tile make it the faster
- *                             one), 2 = register row sweep (nodes of a tile taken row by row,
+ *                             set: the kernel of mode 7, for d = 2 up to m =
+ *                             8, where it is the faster one), 2 = register row sweep (nodes of a tile taken row by row,
  *                             the rows a node reaches kept in registers;
  *                             needs T + 2m <= 32; resolved to 1 elsewhere).
  *                             3 = as 1, with the 2m window factors per
@@ -188,14 +187,14 @@ int nfft_plan(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t N,
  *                             four or eight waves each keep a padded tile
  *                             of some of the groups of four, taken one tile
  *                             row at a time, and sum them in float32 at the
- *                             end in a fixed order. The output is the same padded
- *                             tile as modes 1 .. 5 write. Also float32,
- *                             d = 3, tile edge 8, 2m <= 8: one wave holds
- *                             the padded 3-D tile (one 16 x 16 block per
- *                             plane) and takes four nodes of one tile row
- *                             at a time, one right-hand side per
- *                             work-group. Resolved to 5 (and so on; mode 1
- *                             for d = 3) where not supported.
+ *                             end in a fixed order. The output is the same
+ *                             padded tile as modes 1 .. 5 write. Also d = 3,
+ *                             tile edge 8, 2m <= 8: the padded 3-D tile as
+ *                             one 16 x 16 block per plane, four waves with
+ *                             every fourth plane each, four nodes at a time,
+ *                             one right-hand side per work-group. Resolved
+ *                             to 5 (and so on; mode 1 for d = 3) where not
+ *                             supported.
  *                             Default 1; the row sweep wins with many
  *                             right-hand sides per call, and in float32
  *                             takes two of them per wave when

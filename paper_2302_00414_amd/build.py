@@ -47,6 +47,7 @@ FILE_FLAGS = {
     "interp_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "interp3_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "spread_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "spread3_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "spread_mma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 

@@ -145,10 +145,11 @@ bool spread_tile_preferred(int d, int T, bool f64, int m, int64_t N, int64_t nti
 size_t spread_tile_lds_bytes(int m, bool f64);
 template <typename R>
 hipError_t launch_spread_tile(const SpreadArgs<R>& a, int nrhs, hipStream_t s);
-// The d = 3 form of mode 7: one wave holds the padded tile (tile edge 8,
-// 2m <= 8, nodes sorted by their dimension-0 cell within tiles) in
-// matrix-core accumulators, float32 or float64.
+// The d = 3 form of mode 7 (tile edge 8, 2m <= 8, nodes sorted by their
+// dimension-0 cell within tiles), float32 or float64, and the default mode's
+// kernel where spread3_mma_preferred says so.
 bool spread3_mma_supported(int d, int T, bool f64, int m);
+bool spread3_mma_preferred(int d, int T, bool f64, int m);
 size_t spread3_mma_lds_bytes(bool f64);
 template <typename R>
 hipError_t launch_spread3_mma(const SpreadArgs<R>& a, int nrhs, hipStream_t s);

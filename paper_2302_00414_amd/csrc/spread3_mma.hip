@@ -1,203 +1,243 @@
 // Spreading for d = 3 on the matrix cores, float32 and float64 (Algorithm
 // 2.4 step 1 with the weights of (3.7)), tile edge 8 and 2m <= 8, so that
-// the padded tile of a work item (P = 8 + 2m <= 16 cells per dimension) fits
-// in the accumulators of one wave: plane i0 of the padded tile is one
-// 16 x 16 block (rows i1, columns i2) of v_mfma_f32_16x16x4f32 (float64:
-// v_mfma_f64_16x16x4f64) accumulators, real and imaginary part, 2P blocks in
-// all.
+// plane i0 of the padded tile of a work item (P = 8 + 2m <= 16 cells per
+// dimension) is one 16 x 16 block (rows i1, columns i2) of
+// v_mfma_f32_16x16x4f32 (float64: v_mfma_f64_16x16x4f64) accumulators, real and
+// imaginary part.
 //
 // A node at tile-local cell (l0, l1, l2) reaches the padded cells
 // (l0 + 1 + p0, l1 + 1 + p1, l2 + 1 + p2), p_t < 2m, with the window factors
 // a(p0) b(p1) e(p2), and on a grid plane of dimension t also the closed-edge
-// cell l_t of that dimension. For one plane i0 = l0 + 1 + p0 the update is
-//     G[i0][i1][i2] += sum_n (a_n(p0) b_n[i1] c_n) e_n[i2],
-// a product whose inner dimension runs over the nodes: four nodes of the
-// same tile row l0 = r at a time, lane (k, i) supplies A_k[i] = b_k[i] c_k
-// (real or imaginary part) and B_k[i] = a_k(p0) e_k[i], two operations per
-// plane. The planes a tile row reaches are compile-time constants (the
-// nodes of a tile are sorted by l0 at plan time and the node loop runs
-// inside an unrolled loop over the 8 tile rows and the 2m planes). Lane
-// (k, p) of a node's 16-lane row evaluates window polynomial p at the
-// node's dimension-0 and dimension-1 offsets, lane (k, 8 + p) at its
-// dimension-2 offset; a_k(p0) reaches the lanes of node k by a DPP row
-// broadcast, b_k and e_k by ds_bpermute.
-// The padded tile is written out like the other kernels' (the split-tile
-// sums and the first FFT pass merge the tiles).
+// cell l_t of that dimension. For one plane the update is
+//     G[i0][i1][i2] += sum_n (b_n[i1] c_n) (a_n[i0] e_n[i2]),   c_n = w_n f_n,
+// a product whose inner dimension runs over the nodes, four at a time.
+//
+// Four waves share the nodes of an item, 64 at a time: each evaluates the
+// window of 16 of them and writes the factors to LDS, a row of 16 padded cells
+// per node and dimension, zero where the window does not reach; then wave w
+// takes all groups of four through the planes i0 = w mod 4 (two of the 2m that
+// a node reaches, at m = 4). The rows being zero outside the windows, a group
+// may hold any nodes; they are sorted by l0 at plan time, so that a group
+// reaches few planes more than 2m. No cell is summed by two waves and the order
+// of every sum is fixed. The padded tile is written out like the other
+// kernels' (the split-tile sums and the first FFT pass merge the tiles).
+//
+// Bound: matrix and vector work, which take turns: 16 matrix operations per
+// group of four nodes (m = 4; a quarter of their products is inside the
+// windows) and about 65 vector instructions, half of them the staging. A form
+// with one wave per item, which formed its operands per group and held all
+// planes, took 68.5 us on the jittered set of 524288 nodes at M = 64, m = 4
+// (62.7 here), in float64 151 (113 here). Reading the next group's operands a
+// group ahead costs more in moves than it hides (108 against 100 us for the
+// transform of as many uniform nodes); two groups a step against one 99.7 and
+// 100.1, against four 98.4.
 #include "spread_common.hpp"
 
 namespace nfft {
 
 namespace {
 
-// Per precision: the accumulator block (four elements a lane, column l & 15;
-// row 4 (l >> 4) + v for element v of lane l in float32, 4 v + (l >> 4) in
-// float64), the operation, a lane read and the staged node.
 template <typename R> struct Mma3T;
 template <> struct Mma3T<float> {
-  static constexpr bool kRowsByQuarter = true;
   typedef float v4 __attribute__((ext_vector_type(4)));
   static __device__ __forceinline__ v4 mfma(float a, float b, v4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ float read(float v, int byte_addr) {
-    return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_addr, __float_as_int(v)));
-  }
+  // row of element v of lane quarter q
+  static __device__ __forceinline__ int row(int q, int v) { return 4 * q + v; }
 };
 template <> struct Mma3T<double> {
-  static constexpr bool kRowsByQuarter = false;
   typedef double v4 __attribute__((ext_vector_type(4)));
   static __device__ __forceinline__ v4 mfma(double a, double b, v4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ double read(double v, int byte_addr) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_ds_bpermute(byte_addr, (int)(u & 0xffffffffLL));
-    const int hi = __builtin_amdgcn_ds_bpermute(byte_addr, (int)(u >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-  }
+  static __device__ __forceinline__ int row(int q, int v) { return 4 * v + q; }
 };
 
-// node b: y0, y1, y2, Re c, Im c, edge factor of dimension 1 and of
-// dimension 2 (0 off a grid plane), and a word: -(l1 + 1) in bits 0-7,
-// -(l2 + 1) in bits 8-15, the edge flag of dimension 0 in bit 16, l0 from
-// bit 20
-template <typename R> struct alignas(8 * sizeof(R)) Mma3Node {
-  R y0, y1, y2, cx, cy, e1, e2;
-  int bits;
-};
-
-// sign-extended 8-bit field
-__device__ __forceinline__ int sext8(int v) { return (v << 24) >> 24; }
+constexpr int k3MmaT = 8;
+constexpr int k3Chunk = 64;           // nodes staged at a time
+constexpr int k3Rows = k3Chunk + 4;   // the last group may look past the last node
+constexpr int k3RowFS = 48;           // a (16), b (16), e (16)
 
 }  // namespace
 
-// Nodes staged per batch; one wave per work item.
-constexpr int k3MmaBatch = 256;
-constexpr int k3MmaT = 8;
-
 template <typename R, int MW>
-__global__ __launch_bounds__(64) void spread3_mma_kernel(SpreadArgs<R> a) {
+__global__ __launch_bounds__(256) void spread3_mma_kernel(SpreadArgs<R> a) {
+  using M3 = Mma3T<R>;
+  typedef typename M3::v4 v4;
   constexpr int K2 = 2 * MW;
-  constexpr int T = k3MmaT;
-  constexpr int P = T + K2;
-  constexpr int NB = k3MmaBatch;
+  constexpr int P = k3MmaT + K2;
+  constexpr int NK = (P + 3) / 4;  // planes of a wave: w + 4 k
   constexpr int DEG = PolyDeg<R>::value;
-  typedef typename Mma3T<R>::v4 v4;
-  constexpr bool QR = Mma3T<R>::kRowsByQuarter;
+  constexpr int FS = k3RowFS, NN = k3Chunk;
+  constexpr int UG = 2;  // groups per step
   static_assert(P <= 16, "a plane of the padded tile is one 16 x 16 block");
-  // the staged nodes; entry NB is a node with c = 0 for the missing members
-  // of a row's last group
-  __shared__ Mma3Node<R> st[NB + 1];
-  __shared__ int st_rs[T + 1];
+  __shared__ R tab[k3Rows * FS];
+  __shared__ cplx<R> ct[k3Rows];
 
   const int item = blockIdx.x;
   const int rhs = blockIdx.y;
-  const int lane = threadIdx.x;
-  const int kq = lane >> 4;    // node of the group of four; accumulator row quarter
-  const int j = lane & 15;     // row i1 (A), column i2 (B), polynomial (Horner)
-  const int lrow = lane & 48;  // first lane of this lane's 16-lane row
-  const int pc = (j & 7) < K2 ? (j & 7) : K2 - 1;
-  const bool lo8 = j < 8;
-
-  R cf[DEG + 1];
-#pragma unroll
-  for (int q = 0; q <= DEG; ++q) cf[q] = a.coef[pc * (DEG + 1) + q];
-
-  v4 acc[P][2];
-#pragma unroll
-  for (int i = 0; i < P; ++i) {
-    acc[i][0] = v4{(R)0, (R)0, (R)0, (R)0};
-    acc[i][1] = acc[i][0];
-  }
-
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int kq = lane >> 4;  // node of a group; accumulator row quarter
+  const int j = lane & 15;   // pair and dimension (staging); row i1 (A), column i2 (B)
   const int64_t N = a.g.N;
   const int start = a.item_start[item];
   const int cnt = a.item_count[item];
-  const cplx<R>* f = a.f + rhs * a.f_rs;
   const R edge = a.edge;
+  const cplx<R>* f = a.f + rhs * a.f_rs;
 
-  if (lane == 0) st[NB] = Mma3Node<R>{(R)0, (R)0, (R)0, (R)0, (R)0, (R)0, (R)0, 0};
-  for (int b0 = 0; b0 < cnt; b0 += NB) {
-    const int nb = (cnt - b0) < NB ? (cnt - b0) : NB;
-    __syncthreads();  // the previous batch is consumed
-    // two nodes a lane per step, so that their loads are in flight together
-#pragma unroll 2
-    for (int t = lane; t < nb; t += 64) {
-      const int i = start + b0 + t;
-      const cplx<R> wv = a.w[i];
-      const cplx<R> fv = f[a.perm[i]];
-      const uint32_t L = a.loc[i];
-      const int l0 = (int)(L & kLocMask);
-      const int l1 = (int)((L >> kLocBits) & kLocMask);
-      const int l2 = (int)((L >> (2 * kLocBits)) & kLocMask);
-      st[t] = Mma3Node<R>{(R)2 * a.frac[i] - (R)1, (R)2 * a.frac[N + i] - (R)1,
-                          (R)2 * a.frac[2 * N + i] - (R)1, wv.x * fv.x - wv.y * fv.y,
-                          wv.x * fv.y + wv.y * fv.x,
-                          ((L >> (kEdgeShift + 1)) & 1u) ? edge : (R)0,
-                          ((L >> (kEdgeShift + 2)) & 1u) ? edge : (R)0,
-                          ((-(l1 + 1)) & 0xff) | (((-(l2 + 1)) & 0xff) << 8) |
-                              (int)(((L >> kEdgeShift) & 1u) << 16) | (l0 << 20)};
-    }
-    __syncthreads();
-    // first node of each tile row (the batch is sorted by l0)
-    for (int t = lane; t < nb; t += 64) {
-      const int rt = st[t].bits >> 20;
-      const int rp = t > 0 ? st[t - 1].bits >> 20 : -1;
-      for (int r = rp + 1; r <= rt; ++r) st_rs[r] = t;
-      if (t == nb - 1)
-        for (int r = rt + 1; r <= T; ++r) st_rs[r] = nb;
-    }
-    __syncthreads();
+  // Staging. The window is even: the polynomial of cell 2m - 1 - p is that of
+  // cell p at -y. Of a node's 16 lanes, lane 4 t + p evaluates the even and the
+  // odd part of polynomial p < m at the node's offset in dimension t < 3 and so
+  // both cells, and writes two of the zeros around the window; lanes with p >=
+  // m write four zeros. Cell c of the window is padded cell l + 1 + c; cells
+  // 2m .. 15 go round to the padded cells outside it, cell 15 being the closed
+  // edge l.
+  const int dim = j >> 2 < 3 ? j >> 2 : 2, jj = j & 3;
+  const bool stages = j < 12;
+  const int c1 = jj < MW ? jj : 4 * MW + 4 * (jj - MW);
+  const int c2 = jj < MW ? K2 - 1 - jj : c1 + 1;
+  const int c3 = jj < MW ? K2 + 2 * jj : c1 + 2;
+  const int c4 = c3 + 1;
+  const uint32_t em = jj == 3 ? 1u << (kEdgeShift + dim) : 0u;  // its c4 is cell 15
+  const R* pcf = a.coef + (jj < MW ? jj : 0) * (DEG + 1);
+  R ce[DEG / 2 + 1], co[DEG / 2];
+#pragma unroll
+  for (int t = 0; t <= DEG / 2; ++t) ce[t] = pcf[2 * t];
+#pragma unroll
+  for (int t = 0; t < DEG / 2; ++t) co[t] = pcf[2 * t + 1];
+#pragma unroll
+  for (int t = 0; t <= DEG / 2; ++t) ce[t] = jj < MW ? ce[t] : (R)0;
+#pragma unroll
+  for (int t = 0; t < DEG / 2; ++t) co[t] = jj < MW ? co[t] : (R)0;
 
-    static_for<0, T>([&](auto rc) {
-      constexpr int r = decltype(rc)::value;
-      const int n0 = __builtin_amdgcn_readfirstlane(st_rs[r]);
-      const int n1 = __builtin_amdgcn_readfirstlane(st_rs[r + 1]);
-      for (int g = n0; g < n1; g += 4) {
-        const int n = g + kq;
-        const bool valid = n < n1;
-        const Mma3Node<R> nd = st[valid ? n : NB];
-        const int bits = nd.bits;
-        const int q1 = j + sext8(bits & 0xff);         // window cell of row i1 = j
-        const int q2 = j + sext8((bits >> 8) & 0xff);  // window cell of column i2 = j
-        // lanes p < 8: polynomial p at y0 (hA) and y1 (hB); lanes 8 + p: at y2 (hA)
-        const R hA = horner<R>(cf, lo8 ? nd.y0 : nd.y2);
-        const R hB = horner<R>(cf, nd.y1);
-        const R v1 = Mma3T<R>::read(hB, (lrow | (q1 & 7)) << 2);
-        const R v2 = Mma3T<R>::read(hA, (lrow | 8 | (q2 & 7)) << 2);
-        const R b1 = (unsigned)q1 < (unsigned)K2 ? v1 : (q1 == -1 ? nd.e1 : (R)0);
-        const R e2 = (unsigned)q2 < (unsigned)K2 ? v2 : (q2 == -1 ? nd.e2 : (R)0);
-        const R ur = b1 * nd.cx;
-        const R ui = b1 * nd.cy;
-        static_for<0, K2>([&](auto pc_) {
-          constexpr int p = decltype(pc_)::value;
-          const R bp = row_bcast<p>(hA) * e2;  // a_kq(p) e_kq[i2]
-          acc[r + 1 + p][0] = Mma3T<R>::mfma(ur, bp, acc[r + 1 + p][0]);
-          acc[r + 1 + p][1] = Mma3T<R>::mfma(ui, bp, acc[r + 1 + p][1]);
-        });
-        // closed-edge plane r of nodes on a grid plane of dimension 0
-        const bool e0 = valid && ((bits >> 16) & 1);
-        if (__builtin_amdgcn_ballot_w64(e0)) {
-          const R be = e0 ? edge * e2 : (R)0;
-          acc[r][0] = Mma3T<R>::mfma(ur, be, acc[r][0]);
-          acc[r][1] = Mma3T<R>::mfma(ui, be, acc[r][1]);
-        }
+  // node data of a chunk, in registers one chunk ahead: cell word and one
+  // offset of the four nodes whose factors this lane evaluates, the cell word
+  // of node `lane`, and (wave 0) weight, sample and index of node `lane`. Nodes
+  // past the item's last are its neighbours' or the arrays' padding: their c is
+  // taken as zero.
+  uint32_t Ln[4], Lb;
+  R xn[4];
+  cplx<R> wv = mkc<R>(0, 0), fv = wv;
+  int jn = 0;
+  const uint32_t* loc = a.loc + start;
+  const R* fr = a.frac + start + dim * N + kq;
+  auto load_chunk = [&](int b0) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      Ln[t] = (loc + b0 + 16 * wave + 4 * t)[kq];
+      xn[t] = (fr + b0 + 16 * wave + 4 * t)[0];
+    }
+    Lb = (loc + b0)[lane];
+    if (wave == 0) {
+      wv = (a.w + start + b0)[lane];
+      fv = f[jn];
+      jn = (a.perm + start + b0 + NN)[lane];
+    }
+  };
+  if (wave == 0) jn = (a.perm + start)[lane];
+  load_chunk(0);
+
+  // the rows past a chunk are read by its last group: any finite value will do
+  for (int i = tid; i < (k3Rows - NN) * FS; i += 256) tab[NN * FS + i] = (R)0;
+
+  v4 acc[NK][2];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+    acc[k][0] = v4{(R)0, (R)0, (R)0, (R)0};
+    acc[k][1] = acc[k][0];
+  }
+  const R* opb = tab + kq * FS + 16 + j;  // b row; e row 16 further; a row's plane 4 k: below
+  const R* opa = tab + kq * FS + wave;
+  const cplx<R>* opc = ct + kq;
+
+  for (int b0 = 0; b0 < cnt; b0 += NN) {
+    const int nb = cnt - b0 < NN ? cnt - b0 : NN;
+    if (b0) __syncthreads();  // the previous chunk is consumed
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t L = Ln[t];
+      const R y = (R)2 * xn[t] - (R)1;
+      const R y2 = y * y;
+      R ev = ce[DEG / 2], od = co[DEG / 2 - 1];
+#pragma unroll
+      for (int q = DEG / 2 - 1; q >= 0; --q) ev = ev * y2 + ce[q];
+#pragma unroll
+      for (int q = DEG / 2 - 2; q >= 0; --q) od = od * y2 + co[q];
+      const R v1 = ev + y * od, v2 = ev - y * od;
+      const int l1 = (int)((L >> (kLocBits * dim)) & kLocMask) + 1;
+      R* row = tab + (16 * wave + 4 * t + kq) * FS + 16 * dim;
+      if (stages) {
+        row[(l1 + c1) & 15] = v1;
+        row[(l1 + c2) & 15] = v2;
+        row[(l1 + c3) & 15] = (R)0;
+        row[(l1 + c4) & 15] = L & em ? edge : (R)0;
       }
-    });
+    }
+    if (wave == 0)
+      ct[lane] = mkc<R>(wv.x * fv.x - wv.y * fv.y, wv.x * fv.y + wv.y * fv.x);
+    // planes of lane's group of four that this wave owns, as bits k: from the
+    // group's first plane (a closed edge's if it has one; the nodes are sorted
+    // by l0, but one on a grid plane may begin before its predecessors) to its
+    // last node's last
+    int mask;
+    {
+      const int l0 = (int)(Lb & kLocMask);
+      int first = lane < nb ? l0 + ((Lb >> kEdgeShift) & 1u ? 0 : 1) : P;
+      int last = lane < nb ? l0 + K2 : -1;
+      first = min(first, __shfl_xor(first, 1));
+      first = min(first, __shfl_xor(first, 2));
+      last = max(last, __shfl_xor(last, 1));
+      last = max(last, __shfl_xor(last, 2));
+      const int k0 = (max(first - wave, 0) + 3) >> 2;
+      const int k1 = (last - wave) >> 2;  // -1 before this wave's first plane
+      mask = ((2 << k1) - 1) & ~((1 << k0) - 1);
+      if (last < wave) mask = 0;
+    }
+    __syncthreads();
+    load_chunk(b0 + NN);
+
+    const R* pb = opb;
+    const R* pa = opa;
+    const cplx<R>* pc = opc;
+    auto group = [&](int n, int u, bool part) {
+      const R b = pb[4 * u * FS], e = pb[4 * u * FS + 16];
+      cplx<R> c = pc[4 * u];
+      R an[NK];
+#pragma unroll
+      for (int k = 0; k < NK; ++k) an[k] = pa[4 * u * FS + 4 * k];
+      if (part) c = kq < nb - n ? c : mkc<R>(0, 0);
+      const R br = b * c.x, bi = b * c.y;
+      const int m = __builtin_amdgcn_readlane(mask, n);
+#pragma unroll
+      for (int k = 0; k < NK; ++k)
+        if (m >> k & 1) {
+          const R ae = an[k] * e;
+          acc[k][0] = M3::mfma(br, ae, acc[k][0]);
+          acc[k][1] = M3::mfma(bi, ae, acc[k][1]);
+        }
+    };
+    int n = 0;
+    for (; n + UG * 4 <= nb; n += UG * 4, pb += UG * 4 * FS, pa += UG * 4 * FS, pc += UG * 4)
+#pragma unroll
+      for (int u = 0; u < UG; ++u) group(n + 4 * u, u, false);
+    for (; n < nb; n += 4, pb += 4 * FS, pa += 4 * FS, pc += 4) group(n, 0, n + 4 > nb);
   }
 
-  // accumulator element v of lane l: row i1 = 4 (l >> 4) + v (float64:
-  // 4 v + (l >> 4)), column i2 = l & 15
+  // element v of lane l: row i1, column i2 = l & 15
   const int slot = a.item_slot[item];
   constexpr int Ptot = P * P * P;
   cplx<R>* out = slot < 0 ? a.tilep + rhs * a.tile_rs + (int64_t)a.item_bin[item] * Ptot
                           : a.itemp + rhs * a.item_rs + (int64_t)slot * Ptot;
 #pragma unroll
-  for (int i0 = 0; i0 < P; ++i0)
+  for (int k = 0; k < NK; ++k)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int i1 = QR ? 4 * kq + v : 4 * v + kq;
-      if (i1 < P && j < P) out[(i0 * P + i1) * P + j] = mkc<R>(acc[i0][0][v], acc[i0][1][v]);
+      const int i0 = wave + 4 * k, i1 = M3::row(kq, v);
+      if (i0 < P && i1 < P && j < P)
+        out[(i0 * P + i1) * P + j] = mkc<R>(acc[k][0][v], acc[k][1][v]);
     }
 }
 
@@ -206,10 +246,19 @@ bool spread3_mma_supported(int d, int T, bool f64, int m) {
   return d == 3 && T == k3MmaT && m >= 1 && k3MmaT + 2 * m <= 16;
 }
 
+// The default spread mode takes this kernel for m >= 2, at every density and
+// size measured the faster one (whole transforms, LDS accumulation > this
+// kernel, in us: float32, m = 2, 60000 and 524288 nodes at M = 64 53 > 51, 109 >
+// 73, m = 4 87 > 66, 194 > 100; float64, m = 2 84 > 82, 137 > 119, m = 4 173 >
+// 140, 311 > 191; 1000 nodes at M = 8, m = 4, float32 49 > 27). At m = 1 a node
+// updates 8 cells and either may be the faster one.
+bool spread3_mma_preferred(int d, int T, bool f64, int m) {
+  return m >= 2 && spread3_mma_supported(d, T, f64, m);
+}
+
 // the kernel's staging arrays (static LDS)
 size_t spread3_mma_lds_bytes(bool f64) {
-  return (size_t)(k3MmaBatch + 1) * (f64 ? sizeof(Mma3Node<double>) : sizeof(Mma3Node<float>)) +
-         (k3MmaT + 1) * sizeof(int);
+  return (size_t)k3Rows * (k3RowFS + 2) * (f64 ? sizeof(double) : sizeof(float));
 }
 
 template <typename R>
@@ -219,10 +268,10 @@ hipError_t launch_spread3_mma(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
   if (a.g.nsub == 0) return hipSuccess;
   const dim3 grid(a.g.nsub, nrhs);
   switch (a.g.m) {
-    case 1: hipLaunchKernelGGL((spread3_mma_kernel<R, 1>), grid, dim3(64), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((spread3_mma_kernel<R, 2>), grid, dim3(64), 0, s, a); break;
-    case 3: hipLaunchKernelGGL((spread3_mma_kernel<R, 3>), grid, dim3(64), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((spread3_mma_kernel<R, 4>), grid, dim3(64), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((spread3_mma_kernel<R, 1>), grid, dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((spread3_mma_kernel<R, 2>), grid, dim3(256), 0, s, a); break;
+    case 3: hipLaunchKernelGGL((spread3_mma_kernel<R, 3>), grid, dim3(256), 0, s, a); break;
+    case 4: hipLaunchKernelGGL((spread3_mma_kernel<R, 4>), grid, dim3(256), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

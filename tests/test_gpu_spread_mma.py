@@ -1,6 +1,6 @@
-"""The matrix-core spreading (d = 2, tile edge 16: mode 7 for m <= 7, mode 1
-where it is preferred) against the oracle NFFT, at the sizes where its cuts can
-go wrong: groups of four and chunks of 64 nodes that are not full, one node,
+"""The matrix-core spreading (d = 2, tile edge 16: mode 7 for m <= 7, the default
+mode for m = 8; d = 3, tile edge 8) against the oracle NFFT, at the sizes where
+its cuts can go wrong: groups of four and chunks of 64 nodes that are not full, one node,
 tiles of several work items, empty tiles and bands, nodes on grid lines (closed
 edges; at m = 8 the row edge has its own sums), and right-hand sides that do
 not fill the last work-group.
@@ -50,7 +50,7 @@ def test_spreading(prec, m, kind, M, nrhs):
     x = _nodes(kind, 2 * M)
     N = x.shape[0]
     print(f"[case] {kind} N={N} M={M} m={m} {prec} rhs={nrhs}", flush=True)
-    p = Plan(x, M, 2.0, m, precision=prec, max_rhs=nrhs, tuning={"spread_mode": 7 if m <= 7 else 1})
+    p = Plan(x, M, 2.0, m, precision=prec, max_rhs=nrhs, tuning={"spread_mode": 7} if m <= 7 else None)
     w = (1.0 + 0.5 * wl.complex_normal(N, 8)) / N
     p.set_weights(w)
     f = wl.complex_normal((nrhs, N), 9)
@@ -58,6 +58,40 @@ def test_spreading(prec, m, kind, M, nrhs):
     for r in range(nrhs):
         want = onfft.adjoint(x, w * f[r], M, 2.0, m)
         assert metrics.rel_err(got[r], want) <= TOL[prec], (kind, m, r)
+
+
+def _nodes3(kind, Ms):
+    if kind == "one":
+        return np.array([[0.123, -0.4567, 0.31]])
+    if kind == "sparse":      # groups of four span several planes
+        return wl.uniform_nodes(3 * (Ms // 8) ** 3 + 3, 3, 3)
+    if kind == "crowded":     # one tile of several items, full chunks and a remainder
+        return 0.9 * 8 / Ms * wl.uniform_nodes(2 * 256 + 101, 3, 4) + 4.0 / Ms
+    x = wl.uniform_nodes(701, 3, 5)   # grid planes of each dimension, and the wrap
+    for t in range(3):
+        x[t::4, t] = np.round(x[t::4, t] * Ms) / Ms
+    x[0] = [-0.5, -0.5, -0.5]
+    return x
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("m", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind,M,nrhs", [("one", 8, 1), ("sparse", 16, 1), ("crowded", 8, 1),
+                                         ("lines", 8, 2)])
+def test_spreading_3d(prec, m, kind, M, nrhs):
+    from paper_2302_00414_amd.nfft import Plan
+    x = _nodes3(kind, 2 * M)
+    N = x.shape[0]
+    print(f"[case] 3-D {kind} N={N} M={M} m={m} {prec} rhs={nrhs}", flush=True)
+    w = (1.0 + 0.5 * wl.complex_normal(N, 8)) / N
+    f = wl.complex_normal((nrhs, N), 9)
+    for tuning in ({"spread_mode": 7}, None):
+        p = Plan(x, M, 2.0, m, precision=prec, max_rhs=nrhs, tuning=tuning)
+        p.set_weights(w)
+        got = p.adjoint(torch.from_numpy(f).cuda()).cpu().numpy()
+        for r in range(nrhs):
+            want = onfft.adjoint(x, w * f[r], M, 2.0, m)
+            assert metrics.rel_err(got[r], want) <= TOL[prec], (kind, m, r, tuning)
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
