@@ -845,23 +845,25 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   HIP_TRY(p, hipMemsetAsync(p->perm + N, 0, pad * sizeof(int32_t), s));
   HIP_TRY(p, hipMemsetAsync(p->loc + N, 0, pad * sizeof(uint32_t), s));
   HIP_TRY(p, hipMemsetAsync((R*)p->frac + N * d, 0, pad * sizeof(R), s));
-  HIP_TRY(p, nfft::launch_scatter<R>((const int32_t*)bin, (const int32_t*)rank,
-                                     (const int32_t*)offsets, (const uint32_t*)loc_u,
-                                     (const double*)frac_u, N, d, g.nbins, p->perm, p->loc,
-                                     (R*)p->frac, s));
-  if (d >= 2) {
+  if (d == 1) {
+    HIP_TRY(p, nfft::launch_scatter<R>((const int32_t*)bin, (const int32_t*)rank,
+                                       (const int32_t*)offsets, (const uint32_t*)loc_u,
+                                       (const double*)frac_u, N, d, g.nbins, p->perm, p->loc,
+                                       (R*)p->frac, s));
+  } else {
     // within each tile, nodes ordered by their dimension-0 cell (the register
     // row sweeps and the matrix-core tiles consume them row by row)
     void *perm2, *loc2, *frac2;
     TRY(talloc(&perm2, N * sizeof(int32_t)));
     TRY(talloc(&loc2, N * sizeof(uint32_t)));
     TRY(talloc(&frac2, N * d * sizeof(R)));
-    HIP_TRY(p, nfft::launch_row_sort<R>((const int32_t*)bstart, g.nbins, g.T, N, d, p->perm,
-                                        p->loc, (const R*)p->frac, (int32_t*)perm2,
-                                        (uint32_t*)loc2, (R*)frac2, s));
-    HIP_TRY(p, hipMemcpyAsync(p->perm, perm2, N * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    HIP_TRY(p, hipMemcpyAsync(p->loc, loc2, N * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    HIP_TRY(p, hipMemcpyAsync(p->frac, frac2, N * d * sizeof(R), hipMemcpyDeviceToDevice, s));
+    HIP_TRY(p, nfft::launch_scatter<R>((const int32_t*)bin, (const int32_t*)rank,
+                                       (const int32_t*)offsets, (const uint32_t*)loc_u,
+                                       (const double*)frac_u, N, d, g.nbins, (int32_t*)perm2,
+                                       (uint32_t*)loc2, (R*)frac2, s));
+    HIP_TRY(p, nfft::launch_row_sort<R>((const int32_t*)bstart, g.nbins, g.T, N, d,
+                                        (const int32_t*)perm2, (const uint32_t*)loc2,
+                                        (const R*)frac2, p->perm, p->loc, (R*)p->frac, s));
   }
 
   const size_t ni = std::max<size_t>(1, istart.size());

@@ -36,7 +36,7 @@
 // vector instructions, half of them the staging. Against mode 7's other shape
 // (every wave its own padded tile of a quarter of the groups, summed in LDS
 // at the end), polar set of 262144 nodes, M = 256, float64, whole transforms:
-// m = 3 43.7 -> 34.3 us, m = 6 50.5 -> 45.6, m = 7 67.7 -> 49.3; float32,
+// m = 3 43.7 -> 34.3 us, m = 6 50.5 -> 40.0, m = 7 67.7 -> 49.3; float32,
 // m = 6 30.7 -> 32.6, m = 7 36.3 -> 33.5; 1000003 uniform nodes, M = 512,
 // m = 6: float64 141 -> 108 us, float32 76.6 -> 73.4. Against the LDS
 // accumulation (mode 1): linogram of 2097152 nodes, M = 512, m = 8, float64
@@ -69,7 +69,10 @@ template <> struct TileMma<double> {
 
 constexpr int kTileT = 16;
 constexpr int kTileChunk = 64;             // nodes staged at a time
-constexpr int kTileRows = kTileChunk + 8;  // factor rows: a group and its prefetch may look past the last node
+// factor rows: a chunk's last group may look past its nodes. With four more
+// rows a float64 work-group at m = 6 does not fit four times into a compute
+// unit's LDS (polar set of 262144 nodes: 33.8 against 27.5 us).
+constexpr int kTileRows = kTileChunk + 4;
 constexpr int kTileFS = 48;                // A (16), B of columns 0..15, B of columns 16..31
 
 template <typename R, int MW, int NR>
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int n
   // group: any finite value will do (their c is taken as zero)
   {
     const int z0 = cnt < NN ? cnt : NN;
-    for (int i = tid; i < 8 * FS; i += 256) tab[z0 * FS + i] = (R)0;
+    for (int i = tid; i < (NRow - NN) * FS; i += 256) tab[z0 * FS + i] = (R)0;
   }
 
   // float32: a cell's sum is formed in runs of about RUN groups, in NA
