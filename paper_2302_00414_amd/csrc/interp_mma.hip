@@ -24,7 +24,7 @@
 // reads (2m)^2 cells per node from LDS and evaluates the window again for
 // every right-hand side; here a work-group keeps NR tiles in LDS and one
 // evaluation serves all of them. Spiral of 131072 nodes, M = 256, m = 6, 32
-// right-hand sides: 217 -> 134 us; polar set of 262144 nodes, one: 17.2 -> 16.0.
+// right-hand sides: 217 -> 129 us; polar set of 262144 nodes, one: 17.2 -> 16.0.
 #include "spread_common.hpp"
 
 namespace nfft {
@@ -64,7 +64,7 @@ constexpr int kInterpWaves = 4;
 // against 59.1)
 constexpr int kInterpMinM = 5;
 
-template <int MW>
+template <int MW, int NR>
 struct InterpShape {
   static constexpr int P = kInterpT + 2 * MW;
   static constexpr int KS = (P + 3) / 4;  // steps of four columns
@@ -80,9 +80,18 @@ struct InterpShape {
   // lie in 32 different banks
   static constexpr int FS = 34;
   static constexpr int FO = 16;
-  static constexpr int FN = 16 * FS + 16;  // one dimension of one wave
+  static constexpr int FN = 16 * FS + 16;  // columns, one wave
+  // rows: the same, or for four right-hand sides and m <= 6 only a zero on
+  // either side of the window with the cell clamped, which lets four
+  // work-groups instead of three into a compute unit's LDS (spiral of 131072
+  // nodes, 32 right-hand sides, m = 6: whole transform 163.8 -> 157.9 us; for
+  // one right-hand side the clamps cost 1 to 2 %)
+  static constexpr bool compact = NR == 4 && MW <= 6;
+  static constexpr int RS = compact ? 2 * MW + 3 : FS;
+  static constexpr int RO = compact ? 2 : FO;
+  static constexpr int RN = compact ? (16 * RS + 3) / 4 * 4 : FN;
   static constexpr size_t tile = (size_t)P * PS * sizeof(float2);
-  static constexpr size_t factors = (size_t)kInterpWaves * 2 * FN * sizeof(float);
+  static constexpr size_t factors = (size_t)kInterpWaves * (FN + RN) * sizeof(float);
 };
 
 // The factor rows a wave has written are read by its other lanes: the LDS
@@ -97,11 +106,11 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 template <int MW, int NR>
 __global__ __launch_bounds__(64 * kInterpWaves) void interp_mma_kernel(InterpArgs<float> a, int nrhs) {
-  using S = InterpShape<MW>;
+  using S = InterpShape<MW, NR>;
   using R = float;
   typedef v4f v4;
   constexpr int K2 = 2 * MW;
-  constexpr int P = S::P, PS = S::PS, KS = S::KS, FS = S::FS, FN = S::FN;
+  constexpr int P = S::P, PS = S::PS, KS = S::KS, FS = S::FS, FN = S::FN, RN = S::RN;
   constexpr int NP = (K2 + 3) / 4;  // polynomials per lane
   constexpr int DEG = PolyDeg<R>::value;
   constexpr int NT = 64 * kInterpWaves;
@@ -109,7 +118,7 @@ __global__ __launch_bounds__(64 * kInterpWaves) void interp_mma_kernel(InterpArg
   static_assert(NR == 1 || NR % 2 == 0, "right-hand sides are reduced in pairs");
   extern __shared__ double lds_d[];
   cplx<R>* tiles = reinterpret_cast<cplx<R>*>(lds_d);                 // [NR][P][PS]
-  R* fac = reinterpret_cast<R*>(tiles + (size_t)NR * P * PS);         // [wave][2][FN]
+  R* fac = reinterpret_cast<R*>(tiles + (size_t)NR * P * PS);         // [wave][FN + RN]
 
   const int item = blockIdx.x;
   const int rhs0 = blockIdx.y * NR;
@@ -171,10 +180,10 @@ __global__ __launch_bounds__(64 * kInterpWaves) void interp_mma_kernel(InterpArg
 #pragma unroll
     for (int t = 0; t < NR; ++t) tiles[t * (P * PS) + i] = v[t];
   }
-  for (int i = tid; i < kInterpWaves * 2 * FN / 4; i += NT)
+  for (int i = tid; i < kInterpWaves * (FN + RN) / 4; i += NT)
     reinterpret_cast<v4*>(fac)[i] = v4{(R)0, (R)0, (R)0, (R)0};
-  R* f0 = fac + (wave * 2) * FN + n * FS + S::FO;  // row factors of node n
-  R* f1 = f0 + FN;                                 // column factors
+  R* f1 = fac + wave * (FN + RN) + n * FS + S::FO;       // column factors of node n
+  R* f0 = fac + wave * (FN + RN) + FN + n * S::RS + S::RO;  // row factors
   __syncthreads();
 
   const R edge = a.edge;
@@ -223,7 +232,7 @@ __global__ __launch_bounds__(64 * kInterpWaves) void interp_mma_kernel(InterpArg
         f1[p] = h1;
       }
     }
-    if (q < 2) f0[q * FN - 1] = (L >> (kEdgeShift + q)) & 1u ? edge : (R)0;
+    if (q < 2) (q ? f1 : f0)[-1] = (L >> (kEdgeShift + q)) & 1u ? edge : (R)0;
     wave_lds_fence();
 
     R b[KS];
@@ -235,7 +244,10 @@ __global__ __launch_bounds__(64 * kInterpWaves) void interp_mma_kernel(InterpArg
     for (int rb = r0;;) {
       R ra[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) ra[v] = f0[rb + 4 * q + v - l0 - 1];
+      for (int v = 0; v < 4; ++v) {
+        const int c = rb + 4 * q + v - l0 - 1;
+        ra[v] = f0[S::compact ? min(max(c, -2), K2) : c];
+      }
       const cplx<R>* tr = row_of(rb);
       // the operands of one right-hand side are read while the products of
       // the one before run
@@ -290,14 +302,14 @@ bool interp_mma_supported(int d, int T, bool f64, int m) {
 
 template <int MW, int NR>
 static hipError_t interp_mma_nr(const InterpArgs<float>& a, int nrhs, hipStream_t s) {
-  using S = InterpShape<MW>;
+  using S = InterpShape<MW, NR>;
   hipLaunchKernelGGL((interp_mma_kernel<MW, NR>), dim3(a.nitems, (nrhs + NR - 1) / NR),
                      dim3(64 * kInterpWaves), NR * S::tile + S::factors, s, a, nrhs);
   return hipGetLastError();
 }
 
 // Four right-hand sides a work-group: 32 of them on the spiral of 131072
-// nodes (M = 256, m = 6) take 134 us by four, 133 us by eight (twice the LDS,
+// nodes (M = 256, m = 6) take 134 us by four (129 since), 133 us by eight (twice the LDS,
 // half the work-groups) and 145 us by two.
 template <int MW>
 static hipError_t interp_mma_m(const InterpArgs<float>& a, int nrhs, hipStream_t s) {
