@@ -129,7 +129,7 @@ struct nfft_plan_s {
   Geom g{};
   int maxpop = 0;
   int tune[NFFT_TUNE_COUNT] = {0};   // resolved tuning
-  unsigned asked = 0;                // bits of kSpreadKnobs set by the caller (see picks_kernel)
+  unsigned asked = 0;                // bits of kSpreadKnobs set by the caller (see asked_knobs)
   int item_cut = 0;                  // most nodes of a spreading work item of this plan
   int64_t bytes = 0;                 // workspace bytes owned by this handle
   std::shared_ptr<SharedData> shared; // node data, weights and tables

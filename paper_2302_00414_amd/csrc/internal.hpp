@@ -42,7 +42,7 @@ hipError_t launch_zero_tiles(cplx<R>* tilep, int64_t tile_rs, const int32_t* bin
 
 // Entries past the last node of the plan's node arrays (cell words, offsets,
 // weights, indices), zero.
-constexpr int64_t kNodePad = 256;
+constexpr int64_t kNodePad = 512;
 
 // ------------------------------------------------------- spreading / sums
 // Tile partials: every tile owns a padded-tile slot in `tilep` ([rhs][tile]

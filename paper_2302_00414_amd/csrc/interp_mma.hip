@@ -309,8 +309,8 @@ static hipError_t interp_mma_nr(const InterpArgs<float>& a, int nrhs, hipStream_
 }
 
 // Four right-hand sides a work-group: 32 of them on the spiral of 131072
-// nodes (M = 256, m = 6) take 134 us by four (129 since), 133 us by eight (twice the LDS,
-// half the work-groups) and 145 us by two.
+// nodes (M = 256, m = 6) took 134 us by four, 133 us by eight (twice the LDS,
+// half the work-groups) and 145 us by two; with compact row factors 129 by four.
 template <int MW>
 static hipError_t interp_mma_m(const InterpArgs<float>& a, int nrhs, hipStream_t s) {
   if (nrhs > 2) return interp_mma_nr<MW, 4>(a, nrhs, s);

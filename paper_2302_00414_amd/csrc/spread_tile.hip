@@ -14,8 +14,9 @@
 // band its RB rows are complete, go to the tile in LDS and make room for the
 // rows 16 further down.
 //
-// Four waves share the nodes of an item, 64 at a time: each evaluates the
-// window of 16 of them (lane (k, p) polynomial p at node k's two offsets) and
+// Four waves share the nodes of an item, 64 at a time (NS = 4: sixteen waves,
+// 256 at a time, of which four go on to the sums): each evaluates the window
+// of 16 of them (lane (k, p) polynomial p at node k's two offsets) and
 // writes the factors to LDS in operand order: entry i of a node's A row is
 // the factor of slot i, entries of its two B rows those of padded columns i
 // and 16 + i, zero where the window does not reach. Then every wave owns one
@@ -40,8 +41,8 @@
 // m = 6 30.7 -> 32.6, m = 7 36.3 -> 33.5; 1000003 uniform nodes, M = 512,
 // m = 6: float64 141 -> 108 us, float32 76.6 -> 73.4. Against the LDS
 // accumulation (mode 1): linogram of 2097152 nodes, M = 512, m = 8, float64
-// 541 -> 259 us; 40321 nodes, M = 128, m = 6, 11 right-hand sides, float32
-// 71 -> 39 us. Summing the split tiles here (the last work-group of a tile to
+// 541 -> 247 us; 40321 nodes, M = 128, m = 6, 11 right-hand sides, float32
+// 71 -> 38 us. Summing the split tiles here (the last work-group of a tile to
 // arrive) instead of in a kernel of its own took 36.5 against 32.6 us.
 #include "spread_common.hpp"
 
@@ -68,33 +69,35 @@ template <> struct TileMma<double> {
 };
 
 constexpr int kTileT = 16;
-constexpr int kTileChunk = 64;             // nodes staged at a time
-// factor rows: a chunk's last group may look past its nodes. With four more
-// rows a float64 work-group at m = 6 does not fit four times into a compute
-// unit's LDS (polar set of 262144 nodes: 33.8 against 27.5 us).
-constexpr int kTileRows = kTileChunk + 4;
+constexpr int kTileChunk = 64;             // nodes of a sub-chunk: 16 per staging wave
+// factor rows beyond a chunk: its last group may look past its nodes. With
+// eight of them a float64 work-group at m = 6 does not fit four times into a
+// compute unit's LDS (polar set of 262144 nodes: 33.8 against 27.5 us).
+constexpr int kTilePast = 4;
 constexpr int kTileFS = 48;                // A (16), B of columns 0..15, B of columns 16..31
 
-template <typename R, int MW, int NR>
+template <typename R, int MW, int NR, int NS>
 struct TileLds {
   static constexpr int P = kTileT + 2 * MW;
-  static constexpr size_t tab = (size_t)kTileRows * kTileFS * sizeof(R);
-  static constexpr size_t c = (size_t)2 * NR * kTileRows * sizeof(R);
-  static constexpr size_t edge = MW == 8 ? kTileRows * sizeof(R) : 0;
+  static constexpr int rows = NS * kTileChunk + kTilePast;
+  static constexpr size_t tab = (size_t)rows * kTileFS * sizeof(R);
+  static constexpr size_t c = (size_t)2 * NR * rows * sizeof(R);
+  static constexpr size_t edge = MW == 8 ? rows * sizeof(R) : 0;
   static constexpr size_t tiles = (size_t)NR * P * P * sizeof(cplx<R>);
   static constexpr size_t bytes = tiles + tab + c + edge;
 };
 
 }  // namespace
 
-template <typename R, int MW, int NR>
-__global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int nrhs) {
+template <typename R, int MW, int NR, int NS>
+__global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, int nrhs) {
   using M4 = TileMma<R>;
   typedef typename M4::v4 v4;
   constexpr int K2 = 2 * MW;
   constexpr int P = kTileT + K2;
   constexpr int DEG = PolyDeg<R>::value;
-  constexpr int FS = kTileFS, NN = kTileChunk, NRow = kTileRows;
+  constexpr int FS = kTileFS, NN = NS * kTileChunk, NRow = TileLds<R, MW, NR, NS>::rows;
+  constexpr int NT = 256 * NS;
   constexpr int RB = MW <= 4 ? 8 : MW <= 6 ? 4 : MW == 7 ? 2 : 1;  // rows of a band
   constexpr int NBAND = kTileT / RB;
   constexpr bool F32 = std::is_same<R, float>::value;
@@ -117,25 +120,27 @@ __global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int n
   const int lane = tid & 63;
   const int kq = lane >> 4;  // node of a group; slots 4 kq .. 4 kq + 3 of the result
   const int j = lane & 15;   // polynomial and dimension (staging); operand row or column
-  const int blk = wave & 1, part = wave >> 1;
+  const int sub = wave >> 2;  // sub-chunk this wave stages; those of the first take the sums
+  const int blk = wave & 1, part = (wave >> 1) & 1;
   const int64_t N = a.g.N;
   const int start = a.item_start[item];
   const int cnt = a.item_count[item];
   const R edge = a.edge;
 
   // node data of a chunk, in registers one chunk ahead: cell word and one
-  // offset of the four nodes whose factors this lane evaluates, the cell word
-  // of node `lane`, and (wave r) weight, sample and index of node `lane` for
-  // right-hand side r
-  uint32_t Ln[4], Lb;
+  // offset of the four nodes whose factors this lane evaluates, the cell words
+  // of node `lane` of every sub-chunk, and (wave r of a sub-chunk's) weight,
+  // sample and index of its node `lane` for right-hand side r
+  uint32_t Ln[4], Lb[NS] = {};
   R xn[4];
   cplx<R> wv = mkc<R>(0, 0), fv = wv;
   int jn = 0;
   const uint32_t* loc = a.loc + start;
   const int dim = j >> 3, jj = j & 7;
   const R* fr = a.frac + start + (dim ? N : 0) + kq;
-  const bool cw = wave < nr;
-  const cplx<R>* f = a.f + (rhs0 + (cw ? wave : 0)) * a.f_rs;
+  const int cr = wave & 3, cn = 64 * sub + lane;
+  const bool cw = cr < nr;
+  const cplx<R>* f = a.f + (rhs0 + (cw ? cr : 0)) * a.f_rs;
   // Nodes past the item's last are its neighbours' or the arrays' padding:
   // their cell words are not counted and their c is taken as zero.
   auto load_chunk = [&](int b0) {
@@ -144,14 +149,16 @@ __global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int n
       Ln[t] = (loc + b0 + 16 * wave + 4 * t)[kq];
       xn[t] = (fr + b0 + 16 * wave + 4 * t)[0];
     }
-    Lb = (loc + b0)[lane];
+    if (sub == 0)
+#pragma unroll
+      for (int u = 0; u < NS; ++u) Lb[u] = (loc + b0 + 64 * u)[lane];
     if (cw) {
-      wv = (a.w + start + b0)[lane];
+      wv = (a.w + start + b0)[cn];
       fv = f[jn];
-      jn = (a.perm + start + b0 + NN)[lane];
+      jn = (a.perm + start + b0 + NN)[cn];
     }
   };
-  if (cw) jn = (a.perm + start)[lane];
+  if (cw) jn = (a.perm + start)[cn];
 
   // The window is even: the polynomial of cell 2m - 1 - p is that of cell p
   // at -y. Lane p < m of a node's 16 evaluates the even and the odd part of
@@ -180,7 +187,7 @@ __global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int n
   // group: any finite value will do (their c is taken as zero)
   {
     const int z0 = cnt < NN ? cnt : NN;
-    for (int i = tid; i < (NRow - NN) * FS; i += 256) tab[z0 * FS + i] = (R)0;
+    for (int i = tid; i < (NRow - NN) * FS; i += NT) tab[z0 * FS + i] = (R)0;
   }
 
   // float32: a cell's sum is formed in runs of about RUN groups, in NA
@@ -309,16 +316,28 @@ __global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int n
         if (j == 0) et[16 * wave + 4 * t + kq] = (L >> kEdgeShift) & 1u ? (R)1 : (R)0;
     }
     if (cw) {
-      ct[wave * NRow + lane] = wv.x * fv.x - wv.y * fv.y;
-      ct[(NR + wave) * NRow + lane] = wv.x * fv.y + wv.y * fv.x;
+      ct[cr * NRow + cn] = wv.x * fv.x - wv.y * fv.y;
+      ct[(NR + cr) * NRow + cn] = wv.x * fv.y + wv.y * fv.x;
     }
-    const bool valid = lane < nb;
-    const int mb = valid ? (int)(Lb & kLocMask) / RB : NBAND;
-    const bool has_edge = FULL && __builtin_amdgcn_ballot_w64(valid && ((Lb >> kEdgeShift) & 1u)) != 0;
+    int mb[NS];  // bands
+    bool any_edge = false;
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      const bool valid = 64 * u + lane < nb;
+      mb[u] = valid ? (int)(Lb[u] & kLocMask) / RB : NBAND;
+      if constexpr (FULL)
+        any_edge |= __builtin_amdgcn_ballot_w64(valid && ((Lb[u] >> kEdgeShift) & 1u)) != 0;
+    }
+    const bool has_edge = FULL && any_edge;
     __syncthreads();
-    load_chunk(b0 + NN);
+    if (b0 + NN < cnt) load_chunk(b0 + NN);
+    if (sub) continue;
     for (int n = 0; n < nb;) {
-      const int e = __builtin_popcountll(__builtin_amdgcn_ballot_w64(mb <= band));
+      // the band's end: nodes are sorted by row
+      int e = 0;
+#pragma unroll
+      for (int u = 0; u < NS; ++u)
+        e += __builtin_popcountll(__builtin_amdgcn_ballot_w64(mb[u] <= band));
       // whole groups, four at a time
       for (; n + 16 <= e; n += 16) {
         R A[4], B[4], c[4][NR];
@@ -384,22 +403,24 @@ __global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int n
       run = 0;
     }
   }
-  for (; band < NBAND; ++band) {
-    if constexpr (FULL) {
-      put_row(band);
-      if (band + 1 < NBAND) take(band + 1);
-    } else {
-      take(band);
+  if (sub == 0) {
+    for (; band < NBAND; ++band) {
+      if constexpr (FULL) {
+        put_row(band);
+        if (band + 1 < NBAND) take(band + 1);
+      } else {
+        take(band);
+      }
     }
-  }
-  fold_all();
-  // padded rows 16 .. P - 1: slot s holds row 16 + s
+    fold_all();
+    // padded rows 16 .. P - 1: slot s holds row 16 + s
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int row = 16 + 4 * kq + v;
-    if (row < P && col < P)
+    for (int v = 0; v < 4; ++v) {
+      const int row = 16 + 4 * kq + v;
+      if (row < P && col < P)
 #pragma unroll
-      for (int r = 0; r < NR; ++r) out_lds[2 * ((r * P + row) * P + col)] = total(r, v);
+        for (int r = 0; r < NR; ++r) out_lds[2 * ((r * P + row) * P + col)] = total(r, v);
+    }
   }
   __syncthreads();
 
@@ -411,7 +432,7 @@ __global__ __launch_bounds__(256) void spread_tile_kernel(SpreadArgs<R> a, int n
   for (int r = 0; r < nr; ++r) {
     const float4* src = reinterpret_cast<const float4*>(tiles + r * P * P);
     float4* dst = reinterpret_cast<float4*>(out + (rhs0 + r) * rs);
-    for (int i = tid; i < 2 * P * P / VW; i += 256) dst[i] = src[i];
+    for (int i = tid; i < 2 * P * P / VW; i += NT) dst[i] = src[i];
   }
 }
 
@@ -435,15 +456,16 @@ bool spread_tile_preferred(int d, int T, bool f64, int m, int64_t N, int64_t nti
 }
 
 size_t spread_tile_lds_bytes(int m, bool f64) {
-  // the single right-hand-side form
+  // one right-hand side; float32 at m <= 7 in its largest form
   const size_t P = kTileT + 2 * m, rb = f64 ? 8 : 4;
-  return P * P * 2 * rb + kTileRows * (kTileFS + 3) * rb;
+  const int ns = f64 || m == 8 ? 1 : 4;
+  return P * P * 2 * rb + (ns * kTileChunk + kTilePast) * (kTileFS + 3) * rb;
 }
 
-template <typename R, int MW, int NR>
+template <typename R, int MW, int NR, int NS>
 static hipError_t spread_tile_nr(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
-  hipLaunchKernelGGL((spread_tile_kernel<R, MW, NR>), dim3(a.g.nsub, (nrhs + NR - 1) / NR),
-                     dim3(256), (TileLds<R, MW, NR>::bytes), s, a, nrhs);
+  hipLaunchKernelGGL((spread_tile_kernel<R, MW, NR, NS>), dim3(a.g.nsub, (nrhs + NR - 1) / NR),
+                     dim3(256 * NS), (TileLds<R, MW, NR, NS>::bytes), s, a, nrhs);
   return hipGetLastError();
 }
 
@@ -457,9 +479,18 @@ template <typename R, int MW>
 static hipError_t spread_tile_m(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
   const auto fills = [&](int nr) { return (int64_t)a.g.nsub * ((nrhs + nr - 1) / nr) >= 512; };
   if constexpr (std::is_same<R, float>::value)
-    if (nrhs > 2 && fills(4)) return spread_tile_nr<R, MW, 4>(a, nrhs, s);
-  if (nrhs > 1 && fills(2)) return spread_tile_nr<R, MW, 2>(a, nrhs, s);
-  return spread_tile_nr<R, MW, 1>(a, nrhs, s);
+    if (nrhs > 2 && fills(4)) return spread_tile_nr<R, MW, 4, 1>(a, nrhs, s);
+  if (nrhs > 1 && fills(2)) return spread_tile_nr<R, MW, 2, 1>(a, nrhs, s);
+  // At most one work-group per compute unit, of several chunks: nothing covers
+  // the waits of a chunk's staging, so 16 waves stage four chunks at a time
+  // (float32, whole transforms, against one at a time: 20001 nodes, M = 32,
+  // m = 4, 23.7 -> 20.3 us; 30000, M = 64, m = 4, 23.8 -> 20.7; 40321, M = 128,
+  // m = 6, 16.9 -> 16.0). Not at m = 8 (140000, M = 128: 32.1 -> 32.8), nor in
+  // float64, whose products cover them (4096, M = 32, m = 4: 18.4 -> 19.0).
+  if constexpr (std::is_same<R, float>::value && MW <= 7)
+    if ((int64_t)a.g.nsub * nrhs <= 256 && a.g.N > (int64_t)kTileChunk * a.g.nsub)
+      return spread_tile_nr<R, MW, 1, 4>(a, nrhs, s);
+  return spread_tile_nr<R, MW, 1, 1>(a, nrhs, s);
 }
 
 template <typename R>

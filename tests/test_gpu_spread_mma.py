@@ -60,6 +60,24 @@ def test_spreading(prec, m, kind, M, nrhs):
         assert metrics.rel_err(got[r], want) <= TOL[prec], (kind, m, r)
 
 
+@pytest.mark.parametrize("N", [65, 255, 256, 257, 259, 515])
+@pytest.mark.parametrize("m", [1, 4, 7])
+def test_spreading_of_one_crowded_tile(N, m):
+    """One work item of several chunks, float32: the form that stages four
+    chunks at a time, at the edges of its 64 and 256 nodes."""
+    from paper_2302_00414_amd.nfft import Plan
+    M = 16
+    x = 0.9 * 16 / 32 * wl.uniform_nodes(N, 2, 4) + 8.0 / 32
+    print(f"[case] one tile N={N} M={M} m={m} f32", flush=True)
+    p = Plan(x, M, 2.0, m, precision="f32", tuning={"spread_mode": 7, "spread_threads": 64,
+                                                    "item_nodes": 512})
+    w = (1.0 + 0.5 * wl.complex_normal(N, 8)) / N
+    p.set_weights(w)
+    f = wl.complex_normal(N, 9)
+    got = p.adjoint(torch.from_numpy(f).cuda()).cpu().numpy().reshape(-1)
+    assert metrics.rel_err(got, onfft.adjoint(x, w * f, M, 2.0, m)) <= TOL["f32"]
+
+
 def _nodes3(kind, Ms):
     if kind == "one":
         return np.array([[0.123, -0.4567, 0.31]])
