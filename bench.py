@@ -637,7 +637,7 @@ def spread_kernel_name(t):
     if mode in (5, 7) and T == 16:
         nw = {256: 4, 512: 8}.get(t["spread_threads"], 2)
         if mode == 7:
-            return f"spread_mma_kernel<float, {MW}, {nw}>" if nw > 2 else f"spread_tile_kernel<float, {MW}, 1>"
+            return f"spread_mma_kernel<float, {MW}, {nw}>" if nw > 2 else f"spread_tile_kernel<float, {MW}, 1, 1>"
         return f"spread_reg_kernel<{MW}, {nw}>"
     ws = {3: 1, 4: 2}.get(mode, 0)   # window source of the group kernel
     return (f"spread_group_kernel<float, 2, {MW}, {t['spread_threads']}, "

@@ -39,10 +39,10 @@
 // at the end), polar set of 262144 nodes, M = 256, float64, whole transforms:
 // m = 3 43.7 -> 34.3 us, m = 6 50.5 -> 40.0, m = 7 67.7 -> 49.3; float32,
 // m = 6 30.7 -> 32.6, m = 7 36.3 -> 33.5; 1000003 uniform nodes, M = 512,
-// m = 6: float64 141 -> 108 us, float32 76.6 -> 73.4. Against the LDS
+// m = 6: float64 141 -> 108 us, float32 76.6 -> 69.6. Against the LDS
 // accumulation (mode 1): linogram of 2097152 nodes, M = 512, m = 8, float64
 // 541 -> 247 us; 40321 nodes, M = 128, m = 6, 11 right-hand sides, float32
-// 71 -> 38 us. Summing the split tiles here (the last work-group of a tile to
+// 71 -> 43 us. Summing the split tiles here (the last work-group of a tile to
 // arrive) instead of in a kernel of its own took 36.5 against 32.6 us.
 #include "spread_common.hpp"
 
@@ -101,11 +101,11 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
   constexpr int RB = MW <= 4 ? 8 : MW <= 6 ? 4 : MW == 7 ? 2 : 1;  // rows of a band
   constexpr int NBAND = kTileT / RB;
   constexpr bool F32 = std::is_same<R, float>::value;
-  constexpr int NA = F32 ? (NR == 1 ? 4 : 2) : 1;
-  constexpr int RUN = 8 * NA;  // groups of a run
+  constexpr int NA = F32 ? 4 : 1;
+  constexpr int RUN = 4 * NA;  // groups of a run
   constexpr bool FULL = K2 == 16;  // the window rows fill the slots
   static_assert(FULL || RB + K2 <= 16, "the rows of a band's nodes fit in 16 slots");
-  static_assert(NR <= 4, "wave r loads right-hand side r");
+  static_assert(NR <= 2, "wave r loads right-hand side r");
   extern __shared__ double lds_d[];
   cplx<R>* tiles = reinterpret_cast<cplx<R>*>(lds_d);        // [NR][P][P]
   R* tab = reinterpret_cast<R*>(tiles + NR * P * P);         // [NRow][FS]
@@ -161,7 +161,8 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
   if (cw) jn = (a.perm + start)[cn];
 
   // The window is even: the polynomial of cell 2m - 1 - p is that of cell p
-  // at -y. Lane p < m of a node's 16 evaluates the even and the odd part of
+  // at -y. Lane p < m of a node's 16 evaluates the even and the odd part (c_0
+  // added last, as the roundings before it are then of smaller numbers) of
   // polynomial p at the node's row offset and so both cells, lane 8 + p at its
   // column offset. The entries past the window (its cells 2m .. 15: zeros and,
   // as cell 15, the closed edge) fall to the lanes p >= m.
@@ -191,7 +192,9 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
   }
 
   // float32: a cell's sum is formed in runs of about RUN groups, in NA
-  // interleaved parts, and the runs are added in float64
+  // interleaved parts, which are added in float64. Error against float64 over
+  // the LDS kernel's: 0.96 to 1.01; with runs of twice the
+  // groups, their parts added in float32, 1.02 to 1.06
   v4 acc[NA][NR];
   double big[F32 ? NR : 1][4];
   R er[NR], pend[NR];
@@ -207,9 +210,9 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
   auto fold = [&](int r, auto vc) {
     constexpr int v = decltype(vc)::value;
     if constexpr (F32) {
-      R s = acc[0][r][v] + acc[1][r][v];
-      if constexpr (NA == 4) s += acc[2][r][v] + acc[3][r][v];
-      big[r][v] += (double)s;
+      double s = (double)acc[0][r][v] + (double)acc[1][r][v];
+      if constexpr (NA == 4) s += (double)acc[2][r][v] + (double)acc[3][r][v];
+      big[r][v] += s;
 #pragma unroll
       for (int u = 0; u < NA; ++u) acc[u][r][v] = 0.0f;
     }
@@ -295,11 +298,12 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
       const R y2 = y * y;
       R ev = ce[DEG / 2], od = co[DEG / 2 - 1];
 #pragma unroll
-      for (int q = DEG / 2 - 1; q >= 0; --q) ev = ev * y2 + ce[q];
+      for (int q = DEG / 2 - 1; q >= 1; --q) ev = ev * y2 + ce[q];
 #pragma unroll
       for (int q = DEG / 2 - 2; q >= 0; --q) od = od * y2 + co[q];
-      const R v1 = ev + y * od;
-      R v2 = ev - y * od;
+      const R E = y2 * ev;
+      const R v1 = ce[0] + (E + y * od);
+      R v2 = ce[0] + (E - y * od);
       const int l = (int)((L >> (kLocBits * dim)) & kLocMask);
       const int t1 = (l + 1 + c1) & pm, t2 = (l + 1 + c2) & pm;
       const R ed = L & em ? edge : (R)0;
@@ -353,6 +357,11 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
 #pragma unroll
           for (int r = 0; r < NR; ++r)
             acc[u % NA][r] = M4::mfma(A[u] * c[u][r], B[u], acc[u % NA][r]);
+        if constexpr (F32 && NS > 1)
+          if ((run += 4) >= RUN) {
+            fold_all();
+            run = 0;
+          }
         if constexpr (FULL)
           if (has_edge) {
             edges = true;
@@ -364,26 +373,38 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
             }
           }
       }
-      // the rest of the band in this chunk
+      // the rest of the band in this chunk; its parts from `first` on
+      auto rest = [&](auto fc) {
+        constexpr int first = decltype(fc)::value;
 #pragma unroll
-      for (int u = 0; u < 4; ++u, n += 4) {
-        if (n >= e) break;
-        const bool in = kq < e - n;
-        const R A = opA[n * FS], B = opB[n * FS];
-        R c[NR];
+        for (int u = 0; u < 4; ++u, n += 4) {
+          if (n >= e) break;
+          const bool in = kq < e - n;
+          const R A = opA[n * FS], B = opB[n * FS];
+          R c[NR];
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-          c[r] = opC[r * NRow + n];
-          c[r] = in ? c[r] : (R)0;
-          acc[u % NA][r] = M4::mfma(A * c[r], B, acc[u % NA][r]);
-        }
-        if constexpr (FULL)
-          if (has_edge) {
-            edges = true;
-            const R eb = in ? et[n + kq] * B : (R)0;
-#pragma unroll
-            for (int r = 0; r < NR; ++r) er[r] += eb * c[r];
+          for (int r = 0; r < NR; ++r) {
+            c[r] = opC[r * NRow + n];
+            c[r] = in ? c[r] : (R)0;
+            v4& p = acc[(first + u) % NA][r];
+            p = M4::mfma(A * c[r], B, p);
           }
+          if constexpr (FULL)
+            if (has_edge) {
+              edges = true;
+              const R eb = in ? et[n + kq] * B : (R)0;
+#pragma unroll
+              for (int r = 0; r < NR; ++r) er[r] += eb * c[r];
+            }
+        }
+      };
+      if constexpr (FULL && F32) {  // a row has few groups: every second one starts at part 2
+        if (band & 1)
+          rest(std::integral_constant<int, 2>{});
+        else
+          rest(std::integral_constant<int, 0>{});
+      } else {
+        rest(std::integral_constant<int, 0>{});
       }
       n = e;
       if (n < nb) {  // the band is complete: further nodes lie below it
@@ -397,7 +418,7 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
         if (RB >= 4) run = 0;  // the band's end has added every run
       }
     }
-    run += nb / 4;
+    if constexpr (NS == 1) run += nb / 4;
     if (F32 && run >= RUN) {
       fold_all();
       run = 0;
@@ -448,17 +469,20 @@ bool spread_tile_supported(int d, int T, int m) {
 // m = 4: 32 > 31, 49 > 37, and 64 a tile 26 > 27; m = 6, 30, 64 and 128 a
 // tile: 26 > 29, 31 > 31, 38 > 34; m = 8, 64 and 128 a tile: 35 > 38, 44 > 42.
 // float32: m = 2, 128 and 256 a tile 22 > 23, 33 > 28; m = 3, 30 and 128 a
-// tile 19 > 19, 24 > 23; m = 8, 30 a tile 28 > 26.
+// tile 18 > 19, 23 > 22; m = 8, 30 and 128 a tile 28 > 28, 40 > 32. At m = 8 in
+// float32 the few rows per fold make few tiles slow (64 tiles of 470 nodes, M =
+// 64: 28.8 > 32.2): from 512 tiles on.
 bool spread_tile_preferred(int d, int T, bool f64, int m, int64_t N, int64_t ntiles) {
   if (!spread_tile_supported(d, T, m)) return false;
-  const int per_tile = f64 ? (m <= 3 ? 256 : m <= 5 || m == 8 ? 128 : 64) : (m <= 2 ? 256 : 0);
+  const int per_tile = f64 ? (m <= 3 ? 256 : m <= 5 || m == 8 ? 128 : 64) : (m <= 2 ? 256 : m == 3 || m == 8 ? 64 : 0);
+  if (!f64 && m == 8 && ntiles < 512) return false;
   return N >= ntiles * per_tile;
 }
 
 size_t spread_tile_lds_bytes(int m, bool f64) {
   // one right-hand side; float32 at m <= 7 in its largest form
   const size_t P = kTileT + 2 * m, rb = f64 ? 8 : 4;
-  const int ns = f64 || m == 8 ? 1 : 4;
+  const size_t ns = f64 || m == 8 ? 1 : 4;
   return P * P * 2 * rb + (ns * kTileChunk + kTilePast) * (kTileFS + 3) * rb;
 }
 
@@ -469,23 +493,18 @@ static hipError_t spread_tile_nr(const SpreadArgs<R>& a, int nrhs, hipStream_t s
   return hipGetLastError();
 }
 
-// As many right-hand sides per work-group as leave two work-groups per
-// compute unit: one evaluation of the window serves them all (40321 nodes, M =
-// 128, m = 6, 11 right-hand sides, float32: 43 -> 27 us spreading against one
-// at a time), but 64 tiles of 4 right-hand sides are slower by four (9000
-// nodes, M = 64, m = 8: 27 against 22 us). In float64 the LDS of four tiles
-// would leave one work-group per compute unit.
+// Two right-hand sides per work-group where that leaves two work-groups per
+// compute unit: one evaluation of the window serves both. Four took, spiral of
+// 40321 nodes, M = 128, m = 6, 11 right-hand sides, float32, with the two parts
+// that fit in their registers, 57.4 against 52.0 us.
 template <typename R, int MW>
 static hipError_t spread_tile_m(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
-  const auto fills = [&](int nr) { return (int64_t)a.g.nsub * ((nrhs + nr - 1) / nr) >= 512; };
-  if constexpr (std::is_same<R, float>::value)
-    if (nrhs > 2 && fills(4)) return spread_tile_nr<R, MW, 4, 1>(a, nrhs, s);
-  if (nrhs > 1 && fills(2)) return spread_tile_nr<R, MW, 2, 1>(a, nrhs, s);
+  if (nrhs > 1 && (int64_t)a.g.nsub * ((nrhs + 1) / 2) >= 512)
+    return spread_tile_nr<R, MW, 2, 1>(a, nrhs, s);
   // At most one work-group per compute unit, of several chunks: nothing covers
   // the waits of a chunk's staging, so 16 waves stage four chunks at a time
   // (float32, whole transforms, against one at a time: 20001 nodes, M = 32,
-  // m = 4, 23.7 -> 20.3 us; 30000, M = 64, m = 4, 23.8 -> 20.7; 40321, M = 128,
-  // m = 6, 16.9 -> 16.0). Not at m = 8 (140000, M = 128: 32.1 -> 32.8), nor in
+  // m = 4, 23.7 -> 21.2 us; 40321, M = 128, m = 6, 16.9 -> 16.0). Not at m = 8 (140000, M = 128: 32.1 -> 32.8), nor in
   // float64, whose products cover them (4096, M = 32, m = 4: 18.4 -> 19.0).
   if constexpr (std::is_same<R, float>::value && MW <= 7)
     if ((int64_t)a.g.nsub * nrhs <= 256 && a.g.N > (int64_t)kTileChunk * a.g.nsub)

@@ -1,5 +1,5 @@
 """The matrix-core spreading (d = 2, tile edge 16: mode 7 for m <= 7, the default
-mode for m = 8; d = 3, tile edge 8) against the oracle NFFT, at the sizes where
+mode for m = 8, in float32 from 512 tiles on; d = 3, tile edge 8) against the oracle NFFT, at the sizes where
 its cuts can go wrong: groups of four and chunks of 64 nodes that are not full, one node,
 tiles of several work items, empty tiles and bands, nodes on grid lines (closed
 edges; at m = 8 the row edge has its own sums), and right-hand sides that do
@@ -76,6 +76,24 @@ def test_spreading_of_one_crowded_tile(N, m):
     f = wl.complex_normal(N, 9)
     got = p.adjoint(torch.from_numpy(f).cuda()).cpu().numpy().reshape(-1)
     assert metrics.rel_err(got, onfft.adjoint(x, w * f, M, 2.0, m)) <= TOL["f32"]
+
+
+def test_spreading_m8_of_many_tiles():
+    """m = 8 in float32 takes the matrix cores from 512 tiles on; nodes on grid
+    lines among them."""
+    from paper_2302_00414_amd.nfft import Plan
+    M, m, N, nrhs = 256, 8, 1024 * 65, 3
+    x = wl.uniform_nodes(N, 2, 13)
+    x[::7, 0] = np.round(x[::7, 0] * 2 * M) / (2 * M)
+    x[::9, 1] = np.round(x[::9, 1] * 2 * M) / (2 * M)
+    x = np.where(x >= 0.5, x - 1.0, x)
+    print(f"[case] many tiles N={N} M={M} m={m} f32 rhs={nrhs}", flush=True)
+    p = Plan(x, M, 2.0, m, precision="f32", max_rhs=nrhs)
+    p.set_weights(np.full(N, 1.0 / N))
+    f = wl.complex_normal((nrhs, N), 14)
+    got = p.adjoint(torch.from_numpy(f).cuda()).cpu().numpy()
+    for r in range(nrhs):
+        assert metrics.rel_err(got[r], onfft.adjoint(x, f[r] / N, M, 2.0, m)) <= TOL["f32"], r
 
 
 def _nodes3(kind, Ms):
