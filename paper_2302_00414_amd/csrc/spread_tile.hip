@@ -161,10 +161,12 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
   if (cw) jn = (a.perm + start)[cn];
 
   // The window is even: the polynomial of cell 2m - 1 - p is that of cell p
-  // at -y. Lane p < m of a node's 16 evaluates the even and the odd part (c_0
-  // added last, as the roundings before it are then of smaller numbers) of
-  // polynomial p at the node's row offset and so both cells, lane 8 + p at its
-  // column offset. The entries past the window (its cells 2m .. 15: zeros and,
+  // at -y. Lane p < m of a node's 16 evaluates the sums of the odd terms and of
+  // the even terms from y^2 on of polynomial p at the node's row offset, and
+  // from them both cells, lane 8 + p at its column offset. The last two steps
+  // are Horner's, so that c_0, the largest term, enters in one rounding: float32
+  // errors of whole transforms over the LDS kernel's 0.94 to 1.01, with the
+  // even part closed before the odd one is added 0.94 to 1.02. The entries past the window (its cells 2m .. 15: zeros and,
   // as cell 15, the closed edge) fall to the lanes p >= m.
   R ce[DEG / 2 + 1], co[DEG / 2];
   const R* pcf = a.coef + (jj < MW ? jj : 0) * (DEG + 1);
@@ -192,9 +194,9 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
   }
 
   // float32: a cell's sum is formed in runs of about RUN groups, in NA
-  // interleaved parts, which are added in float64. Error against float64 over
-  // the LDS kernel's: 0.96 to 1.01; with runs of twice the
-  // groups, their parts added in float32, 1.02 to 1.06
+  // interleaved parts, which are added in float64: error against float64 over
+  // the LDS kernel's 0.94 to 1.01; with runs of twice the groups, their parts
+  // added in float32, 1.02 to 1.06
   v4 acc[NA][NR];
   double big[F32 ? NR : 1][4];
   R er[NR], pend[NR];
@@ -301,9 +303,8 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
       for (int q = DEG / 2 - 1; q >= 1; --q) ev = ev * y2 + ce[q];
 #pragma unroll
       for (int q = DEG / 2 - 2; q >= 0; --q) od = od * y2 + co[q];
-      const R E = y2 * ev;
-      const R v1 = ce[0] + (E + y * od);
-      R v2 = ce[0] + (E - y * od);
+      const R v1 = ce[0] + y * (od + y * ev);
+      R v2 = ce[0] - y * (od - y * ev);
       const int l = (int)((L >> (kLocBits * dim)) & kLocMask);
       const int t1 = (l + 1 + c1) & pm, t2 = (l + 1 + c2) & pm;
       const R ed = L & em ? edge : (R)0;
