@@ -100,9 +100,9 @@ int nfft_plan(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t N,
  *                             d = 2: 16, d = 3: 8). Fixed at plan time.
  *   NFFT_TUNE_ITEM_NODES      most nodes in one spreading work item,
  *                             16..65536 (default 256; left at the default,
- *                             a plan whose default spread mode takes the
- *                             kernel of mode 7 joins up to two). Fixed at
- *                             plan time.
+ *                             the kernel of mode 7 joins up to two where the
+ *                             default spread mode takes it and that is
+ *                             faster). Fixed at plan time.
  *   NFFT_TUNE_SPREAD_THREADS  threads of a spreading work-group for d <= 2,
  *                             float32, one right-hand side per work-group:
  *                             64, 128 or 256 (default 128); 512 for spread

@@ -65,12 +65,9 @@ unsigned asked_knobs(const int* tuning, int ntuning) {
 }
 
 // Whether the work-item size is left to the library (neither an entry of the
-// tuning array nor the environment sets it). The matrix-core form of spread
-// mode 1 then takes up to two of the default items of a tile as one: fewer
-// tiles to sum afterwards (linogram of 2097152 nodes, M = 512, m = 8, float64:
-// 320 -> 253 us; polar set of 262144 nodes, M = 256, m = 6, float32: 36.0 ->
-// 32.9 us; 4096 nodes at M = 32, where no tile is split any more: 20.9 ->
-// 18.8 us; never slower in the sets measured, while 1024 nodes an item are).
+// tuning array nor the environment sets it). The plan then also keeps a table
+// of items of twice the size, which the matrix-core kernel of the default
+// spread mode takes where that is the faster way (spread_tile_choice).
 bool default_items(const int* tuning, int ntuning) {
   const int v = tuning && NFFT_TUNE_ITEM_NODES < ntuning ? tuning[NFFT_TUNE_ITEM_NODES] : 0;
   return v == 0 && env_int("NFFT_ITEM_NODES", 0) == 0;
@@ -119,6 +116,26 @@ struct SharedData {
   }
 };
 
+// Spreading work items (runs of nodes of one tile) in launch order, and the
+// tiles cut into several of them, on the device.
+struct ItemTable {
+  int32_t* start = nullptr;        // first node, nodes, tile and itemp slot (-1: the only
+  int32_t* count = nullptr;        // item of its tile) of each item
+  int32_t* bin = nullptr;
+  int32_t* slot = nullptr;
+  int32_t* multi_bin = nullptr;    // split tiles
+  int32_t* multi_first = nullptr;  // first itemp slot of each split tile, nmulti + 1
+  int n = 0, nmulti = 0, nslots = 0;
+  int longest = 0;                 // most nodes of an item
+  nfft::ItemShape shape() const { return {n, longest, nmulti > 0}; }
+};
+
+// An item table on the host.
+struct HostItems {
+  std::vector<int32_t> start, count, bin, slot, multi_bin, multi_first;
+  int nslots = 0;
+};
+
 }  // namespace
 
 struct nfft_plan_s {
@@ -130,7 +147,6 @@ struct nfft_plan_s {
   int maxpop = 0;
   int tune[NFFT_TUNE_COUNT] = {0};   // resolved tuning
   unsigned asked = 0;                // bits of kSpreadKnobs set by the caller (see asked_knobs)
-  int item_cut = 0;                  // most nodes of a spreading work item of this plan
   int64_t bytes = 0;                 // workspace bytes owned by this handle
   std::shared_ptr<SharedData> shared; // node data, weights and tables
   std::string last_error;
@@ -139,14 +155,9 @@ struct nfft_plan_s {
   uint32_t* loc = nullptr;
   void* frac = nullptr;
   void* w = nullptr;
-  int32_t* item_start = nullptr;
-  int32_t* item_count = nullptr;
-  int32_t* item_bin = nullptr;
-  int32_t* item_slot = nullptr;    // itemp slot of an item of a split tile, else -1
-  int32_t* multi_bin = nullptr;    // split tiles
-  int32_t* multi_first = nullptr;  // first itemp slot of each split tile
-  int nmulti = 0;
-  int nslots = 0;                  // itemp slots
+  ItemTable items;                 // spreading work items of at most item_nodes nodes
+  ItemTable joined;                // of at most twice as many; empty: not kept
+  bool join = false;               // whether to keep the joined items
   int32_t* fwd_items = nullptr;    // forward window sums: [nfwd][4] first node, nodes, tile, 0
   int nfwd = 0;
   int32_t* empty_bins = nullptr;   // tiles without nodes (their slots are never written)
@@ -479,7 +490,7 @@ int alloc_workspace(nfft_plan_t p, hipStream_t s) {
   TRY(dalloc(p, &p->tilep, tile_bytes, false));
   // tiles without nodes are never written: their partials stay zero
   HIP_TRY(p, hipMemsetAsync(p->tilep, 0, tile_bytes, s));
-  TRY(dalloc(p, &p->itemp, (size_t)R_ * std::max(1, p->nslots) * g.Ptot * sizeof(cplx<R>), false));
+  TRY(dalloc(p, &p->itemp, (size_t)R_ * std::max(1, p->items.nslots) * g.Ptot * sizeof(cplx<R>), false));
   const int64_t Ms = p->Ms, M = p->M;
   if (d >= 2) TRY(dalloc(p, &p->bufA, (size_t)R_ * ipow(Ms, d - 1) * M * sizeof(cplx<R>), false));
   if (d == 3) TRY(dalloc(p, &p->bufB, (size_t)R_ * Ms * M * M * sizeof(cplx<R>), false));
@@ -728,41 +739,20 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   HIP_TRY(p, hipStreamSynchronize(s));
   if (herr) return fail(p, NFFT_EINVAL, "nodes contain a non-finite coordinate");
 
-  // tile starts and work items (at most kItem nodes of one tile each)
+  // tile starts
   std::vector<int32_t> hstart(g.nbins + 1);
-  std::vector<int32_t> istart, icount, ibin, ifirst(g.nbins + 1);  // ifirst: items of tile b
-  const int kItem = p->item_cut;
   int64_t acc = 0;
   p->maxpop = 0;
   for (int b = 0; b < g.nbins; ++b) {
     hstart[b] = (int32_t)acc;
-    ifirst[b] = (int32_t)istart.size();
     p->maxpop = std::max(p->maxpop, hc[b]);
-    for (int k = 0; k < hc[b]; k += kItem) {
-      istart.push_back((int32_t)(acc + k));
-      icount.push_back(std::min(kItem, hc[b] - k));
-      ibin.push_back(b);
-    }
     acc += hc[b];
   }
   hstart[g.nbins] = (int32_t)acc;
-  ifirst[g.nbins] = (int32_t)istart.size();
-  // split tiles: their items write to their own slots and are summed later
-  std::vector<int32_t> islot(istart.size(), -1), mbin, mfirst;
-  for (int b = 0; b < g.nbins; ++b) {
-    const int n = ifirst[b + 1] - ifirst[b];
-    if (n <= 1) continue;
-    mbin.push_back(b);
-    mfirst.push_back(p->nslots);
-    for (int k = 0; k < n; ++k) islot[ifirst[b] + k] = p->nslots++;
-  }
-  mfirst.push_back(p->nslots);
-  p->nmulti = (int)mbin.size();
   std::vector<int32_t> ebins;
   for (int b = 0; b < g.nbins; ++b)
     if (hc[b] == 0) ebins.push_back(b);
   p->nempty = (int)ebins.size();
-  g.nsub = (int)istart.size();
   // launch order of work items: largest first, so that the work-groups that
   // start last are the small remainders of tiles, in blocks of one item per
   // compute unit whose direction alternates: the first work-groups go one
@@ -784,18 +774,41 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
       std::reverse(order.begin() + b0, order.begin() + std::min(order.size(), b0 + C));
     return order;
   };
-  {
-    const std::vector<int32_t> order = launch_order(icount);
-    auto permute = [&](std::vector<int32_t>& a) {
-      std::vector<int32_t> t(a.size());
-      for (size_t i = 0; i < a.size(); ++i) t[i] = a[order[i]];
-      a.swap(t);
-    };
-    permute(istart);
-    permute(icount);
-    permute(ibin);
-    permute(islot);
-  }
+  // work items of at most K nodes of one tile each, in launch order; the items
+  // of split tiles write to slots of their own and are summed later
+  auto cut_items = [&](int K, ItemTable& t) {
+    HostItems h;
+    for (int b = 0; b < g.nbins; ++b) {
+      const bool split = hc[b] > K;
+      if (split) {
+        h.multi_bin.push_back(b);
+        h.multi_first.push_back(h.nslots);
+      }
+      for (int k = 0; k < hc[b]; k += K) {
+        h.start.push_back(hstart[b] + k);
+        h.count.push_back(std::min(K, hc[b] - k));
+        h.bin.push_back(b);
+        h.slot.push_back(split ? h.nslots++ : -1);
+      }
+    }
+    h.multi_first.push_back(h.nslots);
+    const std::vector<int32_t> order = launch_order(h.count);
+    for (std::vector<int32_t>* v : {&h.start, &h.count, &h.bin, &h.slot}) {
+      std::vector<int32_t> u(v->size());
+      for (size_t i = 0; i < u.size(); ++i) u[i] = (*v)[order[i]];
+      v->swap(u);
+    }
+    t.n = (int)h.start.size();
+    t.nmulti = (int)h.multi_bin.size();
+    t.nslots = h.nslots;
+    t.longest = std::min(K, p->maxpop);
+    return h;
+  };
+  const int K = p->tune[NFFT_TUNE_ITEM_NODES];
+  const HostItems hitems = cut_items(K, p->items);
+  HostItems hjoined;
+  if (p->join && p->items.nmulti > 0) hjoined = cut_items(2 * K, p->joined);
+  g.nsub = p->items.n;
   // work items of the forward's window sums, [n][4]: first node, nodes, tile.
   // Matrix-core form: runs of whole groups of 16 nodes, at most kInterpItem,
   // in tile order, an eighth of them for each XCD (work-group i runs on XCD
@@ -806,13 +819,13 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
     const bool f64 = p->prec == NFFT_F64;
     const bool mma = nfft::interp_mma_supported(d, g.T, f64, p->m) ||
                      nfft::interp3_mma_supported(d, g.T, f64, p->m);
-    const int K = mma ? nfft::kInterpItem : p->tune[NFFT_TUNE_ITEM_NODES];
+    const int Kf = mma ? nfft::kInterpItem : K;
     std::vector<int32_t> it, ic;
     for (int b = 0; b < g.nbins; ++b) {
-      const int n = hc[b], k = (n + K - 1) / K;
+      const int n = hc[b], k = (n + Kf - 1) / Kf;
       for (int j = 0, s0 = 0; j < k; ++j) {
         const int groups = (n - s0 + 15) / 16;
-        const int c = mma ? std::min(n - s0, (groups + k - j - 1) / (k - j) * 16) : std::min(K, n - s0);
+        const int c = mma ? std::min(n - s0, (groups + k - j - 1) / (k - j) * 16) : std::min(Kf, n - s0);
         it.insert(it.end(), {hstart[b] + s0, c, b, 0});
         ic.push_back(c);
         s0 += c;
@@ -866,23 +879,22 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
                                         (const R*)frac2, p->perm, p->loc, (R*)p->frac, s));
   }
 
-  const size_t ni = std::max<size_t>(1, istart.size());
-  TRY(dalloc(p, &p->item_start, ni * sizeof(int32_t)));
-  TRY(dalloc(p, &p->item_count, ni * sizeof(int32_t)));
-  TRY(dalloc(p, &p->item_bin, ni * sizeof(int32_t)));
-  if (!istart.empty()) {
-    HIP_TRY(p, hipMemcpyAsync(p->item_start, istart.data(), istart.size() * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(p, hipMemcpyAsync(p->item_count, icount.data(), icount.size() * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(p, hipMemcpyAsync(p->item_bin, ibin.data(), ibin.size() * 4, hipMemcpyHostToDevice, s));
-  }
-  TRY(dalloc(p, &p->item_slot, ni * sizeof(int32_t)));
-  TRY(dalloc(p, &p->multi_bin, std::max<size_t>(1, mbin.size()) * sizeof(int32_t)));
-  TRY(dalloc(p, &p->multi_first, mfirst.size() * sizeof(int32_t)));
-  if (!islot.empty())
-    HIP_TRY(p, hipMemcpyAsync(p->item_slot, islot.data(), islot.size() * 4, hipMemcpyHostToDevice, s));
-  if (!mbin.empty())
-    HIP_TRY(p, hipMemcpyAsync(p->multi_bin, mbin.data(), mbin.size() * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(p, hipMemcpyAsync(p->multi_first, mfirst.data(), mfirst.size() * 4, hipMemcpyHostToDevice, s));
+  auto upload = [&](const std::vector<int32_t>& h, int32_t** q) {
+    TRY(dalloc(p, q, std::max<size_t>(1, h.size()) * sizeof(int32_t)));
+    if (!h.empty())
+      HIP_TRY(p, hipMemcpyAsync(*q, h.data(), h.size() * 4, hipMemcpyHostToDevice, s));
+    return (int)NFFT_OK;
+  };
+  auto upload_items = [&](const HostItems& h, ItemTable& t) {
+    TRY(upload(h.start, &t.start));
+    TRY(upload(h.count, &t.count));
+    TRY(upload(h.bin, &t.bin));
+    TRY(upload(h.slot, &t.slot));
+    TRY(upload(h.multi_bin, &t.multi_bin));
+    return upload(h.multi_first, &t.multi_first);
+  };
+  TRY(upload_items(hitems, p->items));
+  if (p->joined.n) TRY(upload_items(hjoined, p->joined));
   TRY(dalloc(p, &p->empty_bins, std::max<size_t>(1, ebins.size()) * sizeof(int32_t)));
   if (!ebins.empty())
     HIP_TRY(p, hipMemcpyAsync(p->empty_bins, ebins.data(), ebins.size() * 4, hipMemcpyHostToDevice, s));
@@ -967,21 +979,35 @@ int run_adjoint(nfft_plan_t p, const void* f, void* fhat, int nrhs, hipStream_t 
   sa.f = (const cplx<R>*)f;
   sa.tilep = (cplx<R>*)w.tilep;
   sa.itemp = (cplx<R>*)w.itemp;
-  sa.item_start = p->item_start;
-  sa.item_count = p->item_count;
-  sa.item_bin = p->item_bin;
-  sa.item_slot = p->item_slot;
   sa.coef = (const R*)p->coef;
   sa.f_rs = p->N;
   sa.tile_rs = (int64_t)g.nbins * g.Ptot;
-  sa.item_rs = (int64_t)std::max(1, p->nslots) * g.Ptot;
+  sa.item_rs = (int64_t)std::max(1, p->items.nslots) * g.Ptot;
   sa.edge = (R)(p->b * std::exp(-p->b * p->m));
   sa.g = g;
   sa.nt = p->tune[NFFT_TUNE_SPREAD_THREADS];
   sa.nr = nrhs > 1 ? p->tune[NFFT_TUNE_RHS_PER_GROUP] : 1;
   sa.planes = p->tune[NFFT_TUNE_SPREAD_PLANES];
   sa.mode = p->tune[NFFT_TUNE_SPREAD_MODE];
-  sa.pick = p->asked == 0;
+  const ItemTable* items = &p->items;
+  if (sa.mode == 1 && p->asked == 0 && sa.nr == 1) {
+    // the default mode: the matrix-core kernel of mode 7 where it is the faster
+    // one, for d = 2 on the items or the joined items
+    constexpr bool f64 = std::is_same<R, double>::value;
+    if (nfft::spread_tile_supported(p->d, g.T, p->m)) {
+      const nfft::TileChoice c = nfft::spread_tile_choice(f64, p->m, p->N, nrhs, p->items.shape(),
+                                                          p->joined.shape());
+      if (c != nfft::TileChoice::kLds) sa.mode = 7;
+      if (c == nfft::TileChoice::kJoined) items = &p->joined;
+    } else if (nfft::spread3_mma_preferred(p->d, g.T, f64, p->m)) {
+      sa.mode = 7;
+    }
+  }
+  sa.item_start = items->start;
+  sa.item_count = items->count;
+  sa.item_bin = items->bin;
+  sa.item_slot = items->slot;
+  sa.g.nsub = items->n;
   sa.psi = uses_psi(sa.mode) ? (const R*)p->shared->psi : nullptr;
   if constexpr (std::is_same<R, float>::value) {
     if (sa.mode == 6) {
@@ -1027,9 +1053,9 @@ int run_adjoint(nfft_plan_t p, const void* f, void* fhat, int nrhs, hipStream_t 
   nfft::ReduceArgs<R> ra{};
   ra.tilep = (cplx<R>*)w.tilep;
   ra.itemp = (const cplx<R>*)w.itemp;
-  ra.multi_bin = p->multi_bin;
-  ra.multi_first = p->multi_first;
-  ra.nmulti = p->nmulti;
+  ra.multi_bin = items->multi_bin;
+  ra.multi_first = items->multi_first;
+  ra.nmulti = items->nmulti;
   ra.tile_rs = sa.tile_rs;
   ra.item_rs = sa.item_rs;
   ra.g = g;
@@ -1302,7 +1328,7 @@ int run_adjoint_scratch(nfft_plan_t p, const void* f, void* fhat, int nrhs, hipS
   const size_t cb = sizeof(cplx<R>);
   const int64_t Ms = p->Ms, M = p->M;
   const size_t tile = align256((size_t)nrhs * g.nbins * g.Ptot * cb);
-  const size_t item = align256((size_t)nrhs * std::max(1, p->nslots) * g.Ptot * cb);
+  const size_t item = align256((size_t)nrhs * std::max(1, p->items.nslots) * g.Ptot * cb);
   const size_t bufA = p->d >= 2 ? align256((size_t)nrhs * ipow(Ms, p->d - 1) * M * cb) : 0;
   const size_t bufB = p->d == 3 ? align256((size_t)nrhs * Ms * M * M * cb) : 0;
   const bool gather = p->tune[NFFT_TUNE_SPREAD_MODE] == 6;
@@ -1377,6 +1403,8 @@ int64_t nfft_footprint(int d, int M, double sigma, int m, int64_t N, int precisi
   bytes += M * 8 + Ms * cb;                               // tables
   if (d == 2) bytes += N * 4 * m * rb;                    // window factors (spread mode 3)
   bytes += (nbins + N / std::min(K, nfft::kInterpItem) + 8) * 16;  // forward work items
+  if (nfft::spread_tile_supported(d, T, m))               // the joined spreading items
+    bytes += (nbins + N / (2 * K) + 1) * 4 * 4 + (2 * nbins + 1) * 4;
   return bytes;
 }
 
@@ -1409,7 +1437,6 @@ int nfft_plan_tuned(nfft_plan_t* out, int d, int M, double sigma, int m, int64_t
   p->Ms = oversampled(M, sigma);
   p->b = M_PI * (2.0 - 1.0 / sigma);
   std::copy(tune, tune + NFFT_TUNE_COUNT, p->tune);
-  p->item_cut = tune[NFFT_TUNE_ITEM_NODES];
   Geom& g = p->g;
   g.d = d;
   g.Ms = p->Ms;
@@ -1426,9 +1453,7 @@ int nfft_plan_tuned(nfft_plan_t* out, int d, int M, double sigma, int m, int64_t
   while ((1 << g.Ms_shift) < g.Ms) ++g.Ms_shift;
   g.N = N;
   p->asked = asked_knobs(tuning, ntuning);
-  if (default_items(tuning, ntuning) && !p->asked &&
-      nfft::spread_tile_preferred(d, g.T, precision == NFFT_F64, m, N, g.nbins))
-    p->item_cut *= 2;
+  p->join = default_items(tuning, ntuning) && !p->asked && nfft::spread_tile_supported(d, g.T, m);
   if (hipGetDevice(&p->device) != hipSuccess) {
     free_plan(p);
     return fail(nullptr, NFFT_EDEVICE, "no HIP device available");

@@ -77,7 +77,6 @@ struct SpreadArgs {
                              //   (float32; see launch_spread_gather),
                              // 7 padded tile on the matrix cores (d = 2, 3;
                              //   float32 and float64)
-  bool pick;                 // mode 1 by default: the kernel is the library's choice
   const R* psi;              // d = 2: window factors [N][2m][2] in tile order (mode 3)
 };
 template <typename R>
@@ -139,9 +138,19 @@ hipError_t launch_spread_mma(const SpreadArgs<float>& a, int nrhs, hipStream_t s
 // One padded tile per work-group on the matrix cores (float32 or float64, d =
 // 2, tile edge 16, m <= 8, nodes row-sorted within tiles): mode 7 (m <= 7) in
 // float64, with 64 or 128 threads or for several right-hand sides, and the
-// default mode where spread_tile_preferred says so.
+// default mode (m <= 8) where spread_tile_choice says so.
 bool spread_tile_supported(int d, int T, int m);
-bool spread_tile_preferred(int d, int T, bool f64, int m, int64_t N, int64_t ntiles);
+struct ItemShape {
+  int n;        // work items
+  int longest;  // most nodes of one
+  bool split;   // whether a tile has several
+};
+enum class TileChoice { kLds, kItems, kJoined };
+// What the default mode takes for a call of nrhs right-hand sides: the LDS
+// accumulation, or the tile kernel on the items or on the joined ones (n = 0:
+// there are none).
+TileChoice spread_tile_choice(bool f64, int m, int64_t N, int nrhs, const ItemShape& items,
+                              const ItemShape& joined);
 size_t spread_tile_lds_bytes(int m, bool f64);
 template <typename R>
 hipError_t launch_spread_tile(const SpreadArgs<R>& a, int nrhs, hipStream_t s);

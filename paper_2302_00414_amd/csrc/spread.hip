@@ -518,10 +518,7 @@ hipError_t launch_spread(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
       if (nrhs == 1 && a.nt >= 256) return launch_spread_mma(a, nrhs, s);
     return launch_spread_tile<R>(a, nrhs, s);
   }
-  if (a.mode == 1 && a.pick && spread_tile_preferred(a.g.d, a.g.T, f64, a.g.m, a.g.N, a.g.nbins))
-    return launch_spread_tile<R>(a, nrhs, s);
-  if ((a.mode == 7 && spread3_mma_supported(a.g.d, a.g.T, f64, a.g.m)) ||
-      (a.mode == 1 && a.pick && spread3_mma_preferred(a.g.d, a.g.T, f64, a.g.m)))
+  if (a.mode == 7 && spread3_mma_supported(a.g.d, a.g.T, f64, a.g.m))
     return launch_spread3_mma<R>(a, nrhs, s);
   if constexpr (std::is_same<R, float>::value) {
     if (a.mode == 5 && spread_reg_supported(a.g.d, a.g.T, false))

@@ -462,22 +462,60 @@ bool spread_tile_supported(int d, int T, int m) {
   return d == 2 && T == kTileT && m >= 1 && m <= 8;
 }
 
-// The default spread mode takes this kernel from as many nodes per tile on as it is the
-// faster one, else the LDS accumulation. Per node the LDS kernel pays (2m)^2
-// cell updates and this one a fixed product; per item this one pays more.
-// Whole transforms of uniform nodes, LDS kernel > this kernel, in us. float64,
-// M = 256 (1024 tiles): m = 3, 128 and 256 nodes a tile 29 > 31, 43 > 37;
-// m = 4: 32 > 31, 49 > 37, and 64 a tile 26 > 27; m = 6, 30, 64 and 128 a
-// tile: 26 > 29, 31 > 31, 38 > 34; m = 8, 64 and 128 a tile: 35 > 38, 44 > 42.
-// float32: m = 2, 128 and 256 a tile 22 > 23, 33 > 28; m = 3, 30 and 128 a
-// tile 18 > 19, 23 > 22; m = 8, 30 and 128 a tile 28 > 28, 40 > 32. At m = 8 in
-// float32 the few rows per fold make few tiles slow (64 tiles of 470 nodes, M =
-// 64: 28.8 > 32.2): from 512 tiles on.
-bool spread_tile_preferred(int d, int T, bool f64, int m, int64_t N, int64_t ntiles) {
-  if (!spread_tile_supported(d, T, m)) return false;
-  const int per_tile = f64 ? (m <= 3 ? 256 : m <= 5 || m == 8 ? 128 : 64) : (m <= 2 ? 256 : m == 3 || m == 8 ? 64 : 0);
-  if (!f64 && m == 8 && ntiles < 512) return false;
-  return N >= ntiles * per_tile;
+// The default spread mode's choice. Its lines are from whole transforms (graph
+// replays) of uniform, polar and spiral sets, M = 16 .. 512, 1 to 512 nodes a
+// tile, 1, 2 and 11 right-hand sides; times in us, LDS kernel > this one.
+//
+// Items: joining up to two saves the sum of split tiles, but doubles the chain
+// of chunks that a work-group takes one after the other (float64, m = 6: 6 us, m
+// = 8: 8). It pays where no tile stays split and the chain grows by one chunk at
+// most (16 tiles of 256 uniform nodes, m = 6, 20.4 -> 18.8; of 512 20.4 -> 26.8)
+// or the device is full all the same (4096 tiles of 256 127 -> 99.5), and from
+// three default items per compute unit on (m = 8: 130464 polar nodes on 224
+// tiles 37.4 -> 38.5, 261936 on 856 55.2 -> 55.4, 2097152 uniform ones on 4096
+// 284 -> 233).
+//
+// Kernel: while the LDS kernel has up to two work-groups per compute unit
+// (float64 at m = 8: 300), the longest item is the time of either kernel, with
+// more of them the mean item.
+// float64, few: m = 3, longest 217 15.1 > 16.0, 256 19.2 > 19.4, 289 (joined)
+// 19.0 > 17.5; m = 4, 148 14.2 > 14.5, 217 16.3 > 16.2; m = 6, 71 13.1 > 13.7,
+// 104 14.5 > 14.0; m = 8, 256 on a spiral 26.7 > 27.4 and on uniform nodes 27.2 >
+// 24.5: the LDS kernel. Many: m = 3, mean 192 76.6 > 79.1, 256 (joined) 107 >
+// 92.8; m = 4, 64 25.0 > 25.6, 96 28.1 > 27.9; m = 6, 22 48.6 > 51.6, 64 63.0 >
+// 59.4; m = 8, 96 94.7 > 95.5, 128 116 > 103. At m <= 2 never more than even.
+// float32, few: m = 4, longest 13 11.3 > 10.9, m = 2, 13 10.7 > 10.8, 104 13.4 >
+// 12.4; m = 8, 223 on a spiral 23.2 > 24.7, 256 27.2 > 26.5 but on other spirals
+// 0.98 of the LDS kernel: left to that. Many: m = 2, mean 192 23.3 > 24.1, 256
+// (joined) 31.3 > 27.0; m = 3, 22 17.3 > 18.1, 64 19.2 > 19.4 and, on 4096 tiles,
+// 45.5 > 41.7; m = 4, 22 18.3 > 18.6 and 42.4 > 37.9; m = 8, 45 29.5 > 28.4.
+TileChoice spread_tile_choice(bool f64, int m, int64_t N, int nrhs, const ItemShape& items,
+                              const ItemShape& joined) {
+  bool join = false;
+  if (joined.n > 0) {
+    const int pairs = (nrhs + 1) / 2;  // as the launch below groups them
+    const int64_t groups = (int64_t)joined.n * pairs >= 512 ? pairs : nrhs;
+    join = joined.split ? N * groups >= 3 * 256 * 256
+                        : joined.longest <= 320 || (int64_t)joined.n * nrhs >= 2048 ||
+                              N * groups >= 3 * 256 * 256;
+  }
+  const ItemShape& it = join ? joined : items;
+  const TileChoice tile = join ? TileChoice::kJoined : TileChoice::kItems;
+  const int64_t wgs = (int64_t)items.n * nrhs;
+  int least;
+  if (wgs <= (f64 && m == 8 ? 300 : 512)) {
+    static const int longest64[9] = {0, 513, 513, 256, 160, 160, 100, 100, 513};
+    static const int longest32[9] = {0, 128, 128, 0, 0, 0, 0, 0, 513};
+    least = (f64 ? longest64 : longest32)[m];
+    return it.longest >= least && least <= 512 ? tile : TileChoice::kLds;
+  }
+  static const int mean64[9] = {0, 513, 513, 200, 110, 110, 64, 64, 110};
+  static const int mean32[9] = {0, 200, 200, 64, 0, 0, 0, 0, 64};
+  least = (f64 ? mean64 : mean32)[m];
+  // with tiles still split the sum of their slots takes the gain up to denser
+  // sets (m = 2, mean 264 29.7 > 30.5, 342 47.9 > 41.5)
+  if (m <= 2 && it.split) least = m == 2 && !f64 && wgs >= 1280 ? 300 : 513;
+  return least <= 512 && N >= (int64_t)least * it.n ? tile : TileChoice::kLds;
 }
 
 size_t spread_tile_lds_bytes(int m, bool f64) {

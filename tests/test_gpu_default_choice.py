@@ -1,0 +1,78 @@
+"""The default plan's choices against what they choose from, by time: a choice
+that a rule of sizes makes must not cost what it was made to save.
+
+Bound: the two sides are timed in turn as graph replays, the least of several
+rounds each, which repeat to about 2 %; where the rule errs the difference is 15
+to 40 %. 1.1 separates the two.
+"""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2302_00414_amd import workloads as wl
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def _graph(call):
+    """20 calls in a graph (call keeps its buffers for as long as it lives)."""
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        call()
+    s.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        for _ in range(20):
+            call()
+    return g
+
+
+def _times(calls, rounds=8, reps=5):
+    """Microseconds per call of every callable, timed in turn."""
+    graphs = [_graph(c) for c in calls]
+    best = [float("inf")] * len(calls)
+    for _ in range(rounds):
+        for k, g in enumerate(graphs):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(reps):
+                g.replay()
+            torch.cuda.synchronize()
+            best[k] = min(best[k], (time.perf_counter() - t) / (20 * reps) * 1e6)
+    del graphs
+    return best
+
+
+def _nodes(kind, N, M):
+    return wl.uniform_nodes(N, 2, 1) if kind == "uniform" else wl.spiral_nodes(N, M)
+
+
+@pytest.mark.parametrize("prec,kind,M,N,m,nrhs", [
+    # few tiles above the density at which many would be the faster way
+    ("f64", "spiral", 32, 4096, 2, 1), ("f64", "uniform", 32, 8192, 3, 1),
+    ("f64", "uniform", 64, 32768, 4, 1), ("f64", "spiral", 64, 8192, 8, 1),
+    ("f64", "spiral", 64, 8192, 4, 11), ("f32", "spiral", 64, 8192, 3, 11),
+    ("f64", "uniform", 32, 8192, 6, 2), ("f64", "spiral", 128, 65536, 2, 2),
+    # on the other side of the rule's lines
+    ("f64", "uniform", 32, 4096, 4, 1), ("f32", "uniform", 32, 400, 4, 1),
+    ("f64", "uniform", 256, 120000, 8, 1), ("f32", "uniform", 128, 40321, 6, 11)])
+def test_default_spreading_is_not_slower_than_the_lds_kernel(prec, kind, M, N, m, nrhs):
+    from paper_2302_00414_amd.nfft import Plan
+    print(f"[case] {kind} N={N} M={M} m={m} {prec} rhs={nrhs}", flush=True)
+    x = _nodes(kind, N, M)
+    calls, plans = [], []
+    for tuning in (None, {"spread_mode": 1}):
+        p = Plan(x, M, 2.0, m, precision=prec, max_rhs=nrhs, tuning=tuning)
+        p.set_weights(np.full(N, 1.0 / N))
+        v = torch.randn(nrhs, N, dtype=p.cdtype, device="cuda")
+        out = torch.empty(nrhs, M * M, dtype=p.cdtype, device="cuda")
+        plans.append(p)
+        calls.append(lambda p=p, v=v, out=out: p.adjoint(v, out=out))
+    default, lds = _times(calls)
+    print(f"[time] default {default:.1f} us, LDS kernel {lds:.1f} us", flush=True)
+    assert default <= 1.1 * lds
+    for p in plans:
+        p.close()
