@@ -158,7 +158,8 @@ struct nfft_plan_s {
   ItemTable items;                 // spreading work items of at most item_nodes nodes
   ItemTable joined;                // of at most twice as many; empty: not kept
   bool join = false;               // whether to keep the joined items
-  int32_t* fwd_items = nullptr;    // forward window sums: [nfwd][4] first node, nodes, tile, 0
+  int32_t* fwd_items = nullptr;    // forward window sums on the matrix cores, if supported:
+                                   // [nfwd][4] first node, nodes, tile, 0
   int nfwd = 0;
   int32_t* empty_bins = nullptr;   // tiles without nodes (their slots are never written)
   void* gpart = nullptr;           // spread mode 6 partials [max_rhs][slot][256]
@@ -809,37 +810,29 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   HostItems hjoined;
   if (p->join && p->items.nmulti > 0) hjoined = cut_items(2 * K, p->joined);
   g.nsub = p->items.n;
-  // work items of the forward's window sums, [n][4]: first node, nodes, tile.
-  // Matrix-core form: runs of whole groups of 16 nodes, at most kInterpItem,
+  // work items of the forward's window sums on the matrix cores, [nfwd][4] first
+  // node, nodes, tile, 0: runs of whole groups of 16 nodes, at most kInterpItem,
   // in tile order, an eighth of them for each XCD (work-group i runs on XCD
   // i mod 8): neighbouring tiles read the same grid lines through one L2.
-  // Else runs of at most item_nodes nodes in the launch order above.
+  // Entries without nodes fill the last eighth.
   std::vector<int32_t> fitem;
-  {
-    const bool f64 = p->prec == NFFT_F64;
-    const bool mma = nfft::interp_mma_supported(d, g.T, f64, p->m) ||
-                     nfft::interp3_mma_supported(d, g.T, f64, p->m);
-    const int Kf = mma ? nfft::kInterpItem : K;
-    std::vector<int32_t> it, ic;
+  const bool f64 = p->prec == NFFT_F64;
+  if (nfft::interp_mma_supported(d, g.T, f64, p->m) || nfft::interp3_mma_supported(d, g.T, f64, p->m)) {
+    std::vector<int32_t> it;
     for (int b = 0; b < g.nbins; ++b) {
-      const int n = hc[b], k = (n + Kf - 1) / Kf;
+      const int n = hc[b], k = (n + nfft::kInterpItem - 1) / nfft::kInterpItem;
       for (int j = 0, s0 = 0; j < k; ++j) {
         const int groups = (n - s0 + 15) / 16;
-        const int c = mma ? std::min(n - s0, (groups + k - j - 1) / (k - j) * 16) : std::min(Kf, n - s0);
+        const int c = std::min(n - s0, (groups + k - j - 1) / (k - j) * 16);
         it.insert(it.end(), {hstart[b] + s0, c, b, 0});
-        ic.push_back(c);
         s0 += c;
       }
     }
-    const int n = (int)ic.size(), per = (n + 7) / 8;
-    p->nfwd = mma ? 8 * per : n;
+    const int n = (int)(it.size() / 4), per = (n + 7) / 8;
+    p->nfwd = 8 * per;
     fitem.assign((size_t)4 * p->nfwd, 0);
-    std::vector<int32_t> order;
-    if (!mma) order = launch_order(ic);
-    for (int i = 0; i < n; ++i) {
-      const int from = mma ? i : order[i], to = mma ? (i % per) * 8 + i / per : i;
-      std::copy(it.begin() + 4 * from, it.begin() + 4 * from + 4, fitem.begin() + 4 * to);
-    }
+    for (int i = 0; i < n; ++i)
+      std::copy(it.begin() + 4 * i, it.begin() + 4 * i + 4, fitem.begin() + 4 * ((i % per) * 8 + i / per));
   }
   HIP_TRY(p, hipMemcpyAsync(bstart, hstart.data(), (g.nbins + 1) * sizeof(int32_t),
                             hipMemcpyHostToDevice, s));
@@ -1198,6 +1191,9 @@ int run_forward(nfft_plan_t p, const void* fhat, void* f, int nrhs, hipStream_t 
   ia.grid = (const cplx<R>*)p->grid;
   ia.f = (cplx<R>*)f;
   ia.sub = (const cplx<R>*)sub;
+  ia.item_start = p->items.start;
+  ia.item_count = p->items.count;
+  ia.item_bin = p->items.bin;
   ia.items = p->fwd_items;
   ia.nitems = p->nfwd;
   ia.coef = (const R*)p->coef;
@@ -1402,7 +1398,9 @@ int64_t nfft_footprint(int d, int M, double sigma, int m, int64_t N, int precisi
   bytes += R_ * ipow(Ms, d) * cb;                         // forward grid
   bytes += M * 8 + Ms * cb;                               // tables
   if (d == 2) bytes += N * 4 * m * rb;                    // window factors (spread mode 3)
-  bytes += (nbins + N / std::min(K, nfft::kInterpItem) + 8) * 16;  // forward work items
+  const bool f64 = precision == NFFT_F64;
+  if (nfft::interp_mma_supported(d, T, f64, m) || nfft::interp3_mma_supported(d, T, f64, m))
+    bytes += (nbins + N / nfft::kInterpItem + 8) * 16;    // forward work items
   if (nfft::spread_tile_supported(d, T, m))               // the joined spreading items
     bytes += (nbins + N / (2 * K) + 1) * 4 * 4 + (2 * nbins + 1) * 4;
   return bytes;

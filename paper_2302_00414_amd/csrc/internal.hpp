@@ -192,7 +192,10 @@ struct InterpArgs {
   const cplx<R>* grid;       // full oversampled grid, C order, rhs stride grid_rs
   cplx<R>* f;                // output samples, caller order, rhs stride f_rs
   const cplx<R>* sub;        // if set: f = sub - (window sums), sub in caller order, stride f_rs
-  const int32_t* items;      // [nitems][4] first node, nodes (0: padding), tile, 0
+  const int32_t* item_start; // work items of the spreading (g.nsub)
+  const int32_t* item_count;
+  const int32_t* item_bin;
+  const int32_t* items;      // matrix cores: [nitems][4] first node, nodes (0: padding), tile, 0
   int nitems;
   const R* coef;
   const R* psi;              // d = 2: window factor table [N][2m][2] in tile order, or null
@@ -207,6 +210,9 @@ hipError_t launch_interp(const InterpArgs<R>& a, int nrhs, hipStream_t s);
 // nodes row-sorted within tiles).
 constexpr int kInterpItem = 256;  // most nodes of one of its work items
 bool interp_mma_supported(int d, int T, bool f64, int m);
+// Right-hand sides that one of its work-groups takes in a call of nrhs (1, 2 or
+// 4); 0: the lane-per-node kernel is the faster one.
+int interp_mma_rhs(int m, int64_t N, int nitems, int nrhs);
 hipError_t launch_interp_mma(const InterpArgs<float>& a, int nrhs, hipStream_t s);
 // The d = 3 form (float32, tile edge 8, m = 4).
 bool interp3_mma_supported(int d, int T, bool f64, int m);

@@ -308,14 +308,31 @@ static hipError_t interp_mma_nr(const InterpArgs<float>& a, int nrhs, hipStream_
   return hipGetLastError();
 }
 
-// Four right-hand sides a work-group: 32 of them on the spiral of 131072
-// nodes (M = 256, m = 6) took 134 us by four, 133 us by eight (twice the LDS,
-// half the work-groups) and 145 us by two; with compact row factors 129 by four.
+// Several right-hand sides share the window and the node data of a work-group
+// where that leaves three work-groups per compute unit; with fewer, a work-group
+// is one chain of its right-hand sides and one each is faster. Whole transforms
+// (graph replays), lane-per-node kernel > one > two > four a work-group, in us:
+// m = 8, 8192 uniform nodes, M = 32, 5 of them 15.8 > 14.1 > 16.7 > 21.2 (39 items);
+// m = 6, 65536, M = 128, 8 of them 43.3 > 36.3 > 33.9 > 32.6 (377 items). Of 2988
+// sets, m = 5 .. 8, 1 to 32 of them, 4 are slower than with the lane-per-node
+// kernel by more than 2 %, with 512 instead of 768 13, with 1024 8. By eight instead of
+// four, 32 of them on the spiral of 131072 nodes, M = 256, m = 6, took 133 against
+// 134 us. At m = 5 one a work-group is as fast as the lane-per-node kernel, or up
+// to 8 % slower, on less than 3000 items of 64 nodes or more (131072 spiral
+// nodes, M = 128, 15.3 > 16.6), else up to 1.2 times as fast.
+int interp_mma_rhs(int m, int64_t N, int nitems, int nrhs) {
+  for (int nr = 4; nr > 1; nr /= 2)
+    if (2 * nrhs > nr && (int64_t)nitems * ((nrhs + nr - 1) / nr) >= 768) return nr;
+  return m == kInterpMinM && nitems < 3000 && N >= 64 * (int64_t)nitems ? 0 : 1;
+}
+
 template <int MW>
 static hipError_t interp_mma_m(const InterpArgs<float>& a, int nrhs, hipStream_t s) {
-  if (nrhs > 2) return interp_mma_nr<MW, 4>(a, nrhs, s);
-  if (nrhs == 2) return interp_mma_nr<MW, 2>(a, nrhs, s);
-  return interp_mma_nr<MW, 1>(a, nrhs, s);
+  switch (interp_mma_rhs(MW, a.g.N, a.nitems, nrhs)) {
+    case 4: return interp_mma_nr<MW, 4>(a, nrhs, s);
+    case 2: return interp_mma_nr<MW, 2>(a, nrhs, s);
+    default: return interp_mma_nr<MW, 1>(a, nrhs, s);
+  }
 }
 
 hipError_t launch_interp_mma(const InterpArgs<float>& a, int nrhs, hipStream_t s) {

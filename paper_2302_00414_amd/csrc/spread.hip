@@ -344,7 +344,7 @@ template <typename R, int D, int MW>
 __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   extern __shared__ unsigned char smem_raw[];
   cplx<R>* tile = reinterpret_cast<cplx<R>*>(smem_raw);
-  const int4 it = reinterpret_cast<const int4*>(a.items)[blockIdx.x];
+  const int item = blockIdx.x;
   const int rhs = blockIdx.y;
   const int P = a.g.P;
   const int Ptot = a.g.Ptot;
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   // tile origin (in cells) of this work item's tile, per dimension
   int org[3] = {0, 0, 0};
   {
-    int bb = it.z;
+    int bb = a.item_bin[item];
     for (int t = D - 1; t >= 0; --t) {
       org[t] = (bb % nb) * a.g.T - a.g.m;
       bb /= nb;
@@ -393,7 +393,8 @@ __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   __syncthreads();
 
   const int64_t N = a.g.N;
-  const int start = it.x, cnt = it.y;
+  const int start = a.item_start[item];
+  const int cnt = a.item_count[item];
   cplx<R>* f = a.f + rhs * a.f_rs;
   for (int k = threadIdx.x; k < cnt; k += blockDim.x) {
     const int i = start + k;
@@ -469,7 +470,7 @@ template <typename R, int D, int MW>
 static hipError_t interp_dm(const InterpArgs<R>& a, int nrhs, hipStream_t s) {
   size_t lds = (size_t)a.g.Ptot * sizeof(cplx<R>) +
                (std::is_same<R, double>::value ? 2 * MW * (PolyDeg<R>::value + 1) * sizeof(R) : 0);
-  hipLaunchKernelGGL((interp_kernel<R, D, MW>), dim3(a.nitems, nrhs), dim3(256), lds, s, a);
+  hipLaunchKernelGGL((interp_kernel<R, D, MW>), dim3(a.g.nsub, nrhs), dim3(256), lds, s, a);
   return hipGetLastError();
 }
 
@@ -536,9 +537,11 @@ hipError_t launch_spread(const SpreadArgs<R>& a, int nrhs, hipStream_t s) {
 
 template <typename R>
 hipError_t launch_interp(const InterpArgs<R>& a, int nrhs, hipStream_t s) {
-  if (a.nitems == 0) return hipSuccess;
+  if (a.g.nsub == 0) return hipSuccess;
   if constexpr (std::is_same<R, float>::value) {
-    if (interp_mma_supported(a.g.d, a.g.T, false, a.g.m)) return launch_interp_mma(a, nrhs, s);
+    if (interp_mma_supported(a.g.d, a.g.T, false, a.g.m) &&
+        interp_mma_rhs(a.g.m, a.g.N, a.nitems, nrhs) > 0)
+      return launch_interp_mma(a, nrhs, s);
     if (interp3_mma_supported(a.g.d, a.g.T, false, a.g.m)) return launch_interp3_mma(a, nrhs, s);
   }
   switch (a.g.d) {

@@ -76,3 +76,24 @@ def test_default_spreading_is_not_slower_than_the_lds_kernel(prec, kind, M, N, m
     assert default <= 1.1 * lds
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("kind,M,N,m", [("uniform", 32, 8192, 8), ("uniform", 32, 4096, 6),
+                                        ("spiral", 64, 8192, 5)])
+def test_forward_of_several_right_hand_sides_fills_the_device(kind, M, N, m):
+    """Few work items: five right-hand sides fit beside one another and take
+    little longer than one (the grid and its FFT are a few microseconds), where
+    one after the other in a work-group they took 1.4 to 1.6 times as long."""
+    from paper_2302_00414_amd.nfft import Plan
+    print(f"[case] forward {kind} N={N} M={M} m={m} f32", flush=True)
+    p = Plan(_nodes(kind, N, M), M, 2.0, m, precision="f32", max_rhs=5)
+    calls = []
+    for nrhs in (1, 5):
+        v = torch.randn(nrhs, M * M, dtype=p.cdtype, device="cuda")
+        out = torch.empty(nrhs, N, dtype=p.cdtype, device="cuda")
+        calls.append(lambda v=v, out=out: p.forward(v, out=out))
+    one, five = _times(calls)
+    print(f"[time] one {one:.1f} us, five {five:.1f} us", flush=True)
+    assert five <= 1.25 * one
+    calls.clear()
+    p.close()

@@ -78,3 +78,24 @@ def test_window_sums_3d(m, kind, M, nrhs):
     for r in range(nrhs):
         want = onfft.forward(x, h[r].astype(np.complex128), M, 2.0, m)
         assert metrics.rel_err(got[r], want) <= TOL, (kind, m, r)
+
+
+@pytest.mark.parametrize("m", [5, 6, 7, 8])
+@pytest.mark.parametrize("nrhs", [1, 5, 6, 10, 11])
+def test_right_hand_sides_of_a_work_group(m, nrhs):
+    """256 tiles, one of two work items: with 10 and 11 right-hand sides four
+    share a work-group (the last takes two and three), with 5 and 6 two (the last
+    one or two)."""
+    from paper_2302_00414_amd.nfft import Plan
+    M = 128
+    x = np.concatenate([wl.uniform_nodes(256 * 24, 2, 8),
+                        0.9 * 16 / (2 * M) * wl.uniform_nodes(300, 2, 9) + 8.0 / (2 * M)])
+    x[::11, 0] = np.round(x[::11, 0] * 2 * M) / (2 * M)
+    x = np.where(x >= 0.5, x - 1.0, x)
+    print(f"[case] N={x.shape[0]} M={M} m={m} rhs={nrhs}", flush=True)
+    p = Plan(x, M, 2.0, m, precision="f32", max_rhs=nrhs)
+    h = wl.complex_normal((nrhs, M * M), 10).astype(np.complex64)
+    got = p.forward(torch.from_numpy(h).cuda()).cpu().numpy()
+    for r in range(nrhs):
+        want = onfft.forward(x, h[r].astype(np.complex128), M, 2.0, m)
+        assert metrics.rel_err(got[r], want) <= TOL, (m, r)
