@@ -992,7 +992,7 @@ int run_adjoint(nfft_plan_t p, const void* f, void* fhat, int nrhs, hipStream_t 
                                                           p->joined.shape());
       if (c != nfft::TileChoice::kLds) sa.mode = 7;
       if (c == nfft::TileChoice::kJoined) items = &p->joined;
-    } else if (nfft::spread3_mma_preferred(p->d, g.T, f64, p->m)) {
+    } else if (nfft::spread3_mma_preferred(p->d, g.T, f64, p->m, p->N, nrhs, p->items.shape())) {
       sa.mode = 7;
     }
   }

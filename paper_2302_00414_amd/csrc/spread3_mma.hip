@@ -250,13 +250,19 @@ bool spread3_mma_supported(int d, int T, bool f64, int m) {
   return d == 3 && T == k3MmaT && m >= 1 && k3MmaT + 2 * m <= 16;
 }
 
-// The default spread mode takes this kernel for m >= 2, at every density and
-// size measured the faster one (whole transforms, LDS accumulation > this
-// kernel, in us: float32, m = 2, 60000 and 524288 nodes at M = 64 53 > 51, 109 >
-// 73, m = 4 87 > 66, 194 > 100; float64, m = 2 84 > 82, 137 > 119, m = 4 173 >
-// 140, 311 > 191; 1000 nodes at M = 8, m = 4, float32 49 > 27). At m = 1 a node
+// The default spread mode takes this kernel for m >= 2 (whole transforms of
+// uniform nodes at M = 64, 0.1 to 400 a tile, LDS accumulation > this kernel, in
+// us; 409, 8192, 131072 and 1638400 nodes: float32, m = 2 35.4 > 34.6, 44.8 >
+// 45.3, 58.6 > 51.2, 273 > 172; m = 3 39.7 > 38.6, 54.9 > 49.8, 75.8 > 57.7, 428 >
+// 244; m = 4 48.2 > 45.5, 73.6 > 59.6, 99.5 > 69.3, 592 > 297; float64, m = 2
+// 57.9 > 57.2, 77.8 > 74.0, 87.7 > 84.2, 408 > 326; m = 3 69.4 > 67.6, 98.4 >
+// 87.0, 122 > 101, 706 > 460; smaller grids alike). The one exception: at m = 2 in
+// float32 a device full of items of a few nodes each, where its fixed share of
+// an item shows (three right-hand sides, 8192 nodes 90.3 > 93.7, 32768, eight a
+// tile, 99.3 > 102.0; one, 131072, 32 a tile, 58.6 > 51.2). At m = 1 a node
 // updates 8 cells and either may be the faster one.
-bool spread3_mma_preferred(int d, int T, bool f64, int m) {
+bool spread3_mma_preferred(int d, int T, bool f64, int m, int64_t N, int nrhs, const ItemShape& items) {
+  if (m == 2 && !f64 && (int64_t)items.n * nrhs >= 2048 && N < 16 * (int64_t)items.n) return false;
   return m >= 2 && spread3_mma_supported(d, T, f64, m);
 }
 

@@ -97,3 +97,31 @@ def test_forward_of_several_right_hand_sides_fills_the_device(kind, M, N, m):
     assert five <= 1.25 * one
     calls.clear()
     p.close()
+
+
+@pytest.mark.parametrize("d,M,N,m,nrhs,mode", [
+    # 3-D: many items of a few nodes at m = 2, m = 1
+    (3, 64, 8192, 2, 3, 1), (3, 64, 8192, 2, 1, 1), (3, 32, 60000, 2, 1, 7), (3, 16, 500, 2, 1, 7),
+    (3, 64, 8192, 3, 1, 7), (3, 16, 3000, 1, 1, 1),
+    # 2-D, few work-groups: by the longest item
+    (2, 32, 400, 2, 1, 1), (2, 32, 2400, 2, 1, 7), (2, 32, 400, 3, 1, 7), (2, 32, 2400, 8, 3, 1),
+    # many: by the mean item
+    (2, 256, 1024 * 100, 2, 1, 1), (2, 256, 1024 * 50, 3, 1, 1), (2, 256, 1024 * 80, 3, 1, 7),
+    (2, 256, 1024 * 5, 4, 1, 7)])
+def test_float32_default_runs_the_kernel_of(d, M, N, m, nrhs, mode):
+    """Each kernel adds in one order of its own: the default plan gives the bits
+    of the mode whose kernel the rule takes, and not those of the other."""
+    from paper_2302_00414_amd.nfft import Plan
+    print(f"[case] d={d} N={N} M={M} m={m} f32 rhs={nrhs} -> mode {mode}", flush=True)
+    x = wl.uniform_nodes(N, d, 1)
+    v = torch.from_numpy(wl.complex_normal((nrhs, N), 2)).to(torch.complex64).cuda()
+    out = {}
+    for t in (None, 1, 7):
+        p = Plan(x, M, 2.0, m, precision="f32", max_rhs=nrhs, tuning=t and {"spread_mode": t})
+        p.set_weights(np.full(N, 1.0 / N))
+        out[t] = torch.view_as_real(p.adjoint(v))
+        p.close()
+    other = 8 - mode
+    assert torch.equal(out[None], out[mode])
+    if m < 8:
+        assert not torch.equal(out[None], out[other])
