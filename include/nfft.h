@@ -126,11 +126,17 @@ int nfft_plan(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t N,
  *                             2 = two groups per node, one for the real and
  *                             one for the imaginary plane (default 1).
  *   NFFT_TUNE_SPREAD_MODE     single right-hand-side spreading for d = 2:
- *                             1 = accumulation in LDS tiles (as the default,
- *                             with neither the mode nor the threads or planes
- *                             set: the kernel of mode 7, for d = 2 up to m =
- *                             8, where it is the faster one), 2 = register row sweep (nodes of a tile taken row by row,
- *                             the rows a node reaches kept in registers;
+ *                             1 = accumulation in LDS tiles; as the default,
+ *                             with none of the mode, the threads and the
+ *                             planes set: where it is the faster one, the
+ *                             kernel of mode 7 (for d = 2 up to m = 8). An
+ *                             array that sets all three to their defaults,
+ *                             as nfft_get_tuning reports such a plan, counts
+ *                             as one that sets none (with the default item
+ *                             size also for that), so that a plan of a
+ *                             reported tuning runs the same kernels. 2 =
+ *                             register row sweep (nodes of a tile taken row
+ *                             by row, the rows a node reaches kept in registers;
  *                             needs T + 2m <= 32; resolved to 1 elsewhere).
  *                             3 = as 1, with the 2m window factors per
  *                             dimension of every node read from a table
@@ -223,7 +229,12 @@ int nfft_plan_tuned(nfft_plan_t *out, int d, int M, double sigma, int m, int64_t
                     const double *nodes, int precision, int max_rhs, const int *tuning,
                     int ntuning, void *stream);
 
-/* nfft_get_tuning -- the plan's resolved tuning into out[0..n-1], n <= NFFT_TUNE_COUNT. */
+/*
+ * nfft_get_tuning -- the plan's resolved tuning into out[0..n-1], n <=
+ * NFFT_TUNE_COUNT. nfft_plan_tuned with the whole array makes the same plan
+ * again, but for one whose mode was set to 1 beside default threads and planes:
+ * that is reported as the default.
+ */
 int nfft_get_tuning(nfft_plan_t plan, int *out, int n);
 
 /*

@@ -48,29 +48,39 @@ int default_tuning(int knob, int d) {
   }
 }
 
-// The knobs that ask for the LDS kernel of spread mode 1: the mode itself, its
-// threads and its tile layout. A plan with none of them set, in the tuning or
-// in the environment, leaves the kernel of the default mode to the library.
+// The knobs that ask for a kernel: the mode, the threads and the tile layout. A
+// plan with none of them set, in the tuning or in the environment, leaves the
+// kernel of the default mode to the library, and so does one with all three set
+// to the defaults, which is how nfft_get_tuning reports the former.
 const std::pair<int, const char*> kSpreadKnobs[] = {
     {NFFT_TUNE_SPREAD_MODE, "NFFT_SPREAD_MODE"},
     {NFFT_TUNE_SPREAD_THREADS, "NFFT_SPREAD_THREADS"},
     {NFFT_TUNE_SPREAD_PLANES, "NFFT_SPREAD_PLANES"}};
 
-unsigned asked_knobs(const int* tuning, int ntuning) {
+unsigned asked_knobs(const int* tuning, int ntuning, int d) {
   unsigned m = 0;
-  for (const auto& k : kSpreadKnobs)
-    if ((tuning && k.first < ntuning && tuning[k.first]) || env_int(k.second, 0))
-      m |= 1u << k.first;
-  return m;
+  bool env = false, defaults = true;
+  for (const auto& k : kSpreadKnobs) {
+    const int v = tuning && k.first < ntuning ? tuning[k.first] : 0;
+    const bool e = env_int(k.second, 0) != 0;
+    if (v || e) m |= 1u << k.first;
+    env |= e;
+    defaults &= v == default_tuning(k.first, d);
+  }
+  return defaults && !env ? 0 : m;
 }
 
 // Whether the work-item size is left to the library (neither an entry of the
-// tuning array nor the environment sets it). The plan then also keeps a table
-// of items of twice the size, which the matrix-core kernel of the default
-// spread mode takes where that is the faster way (spread_tile_choice).
-bool default_items(const int* tuning, int ntuning) {
-  const int v = tuning && NFFT_TUNE_ITEM_NODES < ntuning ? tuning[NFFT_TUNE_ITEM_NODES] : 0;
-  return v == 0 && env_int("NFFT_ITEM_NODES", 0) == 0;
+// tuning array nor the environment sets it, or the array is a reported one with
+// the default size). The plan then also keeps a table of items of twice the
+// size, which the matrix-core kernel of the default spread mode takes where that
+// is the faster way (spread_tile_choice).
+bool default_items(const int* tuning, int ntuning, int d) {
+  auto at = [&](int k) { return tuning && k < ntuning ? tuning[k] : 0; };
+  const int v = at(NFFT_TUNE_ITEM_NODES);
+  const bool reported = at(NFFT_TUNE_SPREAD_MODE) && asked_knobs(tuning, ntuning, d) == 0;
+  return env_int("NFFT_ITEM_NODES", 0) == 0 &&
+         (v == 0 || (reported && v == default_tuning(NFFT_TUNE_ITEM_NODES, d)));
 }
 
 thread_local std::string g_noplan_error;
@@ -950,6 +960,18 @@ struct Work {
   void* gft;
 };
 
+// What the default mode takes for a call of nrhs right-hand sides, one per
+// work-group: the LDS kernel, or the matrix-core kernel of mode 7 where it is the
+// faster one, for d = 2 on the items or the joined items.
+nfft::TileChoice default_choice(nfft_plan_t p, int nrhs) {
+  const bool f64 = p->prec == NFFT_F64;
+  if (nfft::spread_tile_supported(p->d, p->g.T, p->m))
+    return nfft::spread_tile_choice(f64, p->m, p->N, nrhs, p->items.shape(), p->joined.shape());
+  return nfft::spread3_mma_preferred(p->d, p->g.T, f64, p->m, p->N, nrhs, p->items.shape())
+             ? nfft::TileChoice::kItems
+             : nfft::TileChoice::kLds;
+}
+
 // With accumulate, the last FFT pass adds its outputs to fhat instead of
 // writing them (fhat += A^* W f). With wk, the intermediate buffers are wk's
 // instead of the plan's workspace (no stage events are recorded then).
@@ -984,17 +1006,9 @@ int run_adjoint(nfft_plan_t p, const void* f, void* fhat, int nrhs, hipStream_t 
   sa.mode = p->tune[NFFT_TUNE_SPREAD_MODE];
   const ItemTable* items = &p->items;
   if (sa.mode == 1 && p->asked == 0 && sa.nr == 1) {
-    // the default mode: the matrix-core kernel of mode 7 where it is the faster
-    // one, for d = 2 on the items or the joined items
-    constexpr bool f64 = std::is_same<R, double>::value;
-    if (nfft::spread_tile_supported(p->d, g.T, p->m)) {
-      const nfft::TileChoice c = nfft::spread_tile_choice(f64, p->m, p->N, nrhs, p->items.shape(),
-                                                          p->joined.shape());
-      if (c != nfft::TileChoice::kLds) sa.mode = 7;
-      if (c == nfft::TileChoice::kJoined) items = &p->joined;
-    } else if (nfft::spread3_mma_preferred(p->d, g.T, f64, p->m, p->N, nrhs, p->items.shape())) {
-      sa.mode = 7;
-    }
+    const nfft::TileChoice c = default_choice(p, nrhs);
+    if (c != nfft::TileChoice::kLds) sa.mode = 7;
+    if (c == nfft::TileChoice::kJoined) items = &p->joined;
   }
   sa.item_start = items->start;
   sa.item_count = items->count;
@@ -1450,8 +1464,8 @@ int nfft_plan_tuned(nfft_plan_t* out, int d, int M, double sigma, int m, int64_t
   g.Ms_shift = 0;
   while ((1 << g.Ms_shift) < g.Ms) ++g.Ms_shift;
   g.N = N;
-  p->asked = asked_knobs(tuning, ntuning);
-  p->join = default_items(tuning, ntuning) && !p->asked && nfft::spread_tile_supported(d, g.T, m);
+  p->asked = asked_knobs(tuning, ntuning, d);
+  p->join = default_items(tuning, ntuning, d) && !p->asked && nfft::spread_tile_supported(d, g.T, m);
   if (hipGetDevice(&p->device) != hipSuccess) {
     free_plan(p);
     return fail(nullptr, NFFT_EDEVICE, "no HIP device available");
@@ -1545,9 +1559,9 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
   if (d == 2) modes = {1, 2, 3, 4, 7};
   if (d == 2 && f32) modes = {1, 2, 3, 4, 5, 7};
   if (d == 3) modes = {1, 7};
-  // the tile shape of mode 7 at m = 8 (where mode 7 itself is not defined) as the
-  // default mode's choice
-  if (d == 2 && m == 8) modes.push_back(0);
+  // where the kernel takes no thread count, mode 1 with another than the default
+  // asks for the LDS kernel where the library's choice is a different one
+  if (d >= 2 && !(d == 2 && f32)) threads = {128, 64};
   // the grid-tile gather holds 32 right-hand sides in the lanes of a wave;
   // its units also try 768 list entries (fewer split tiles than 512, fewer
   // long units than 1024)
@@ -1563,7 +1577,8 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
   for (int T : tiles) {
     if (T > Ms) continue;
     for (int K : items) {
-      int tune[NFFT_TUNE_COUNT] = {T, K, 0, 0, 0, 0, 0};
+      // the default item size by its zero, as a plan of the winner's tuning has it
+      int tune[NFFT_TUNE_COUNT] = {T, K == default_tuning(NFFT_TUNE_ITEM_NODES, d) ? 0 : K, 0, 0, 0, 0, 0};
       int resolved[NFFT_TUNE_COUNT];
       if (resolve_tuning(d, Ms, m, precision, tune, NFFT_TUNE_COUNT, resolved, nullptr) != NFFT_OK)
         continue;
@@ -1592,7 +1607,7 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
         for (int pl : planes)
           for (int nr : rpg) {
             int in[NFFT_TUNE_COUNT];
-            std::copy(p->tune, p->tune + NFFT_TUNE_COUNT, in);
+            std::copy(resolved, resolved + NFFT_TUNE_COUNT, in);
             if (nt) in[NFFT_TUNE_SPREAD_THREADS] = nt;
             if (pl) in[NFFT_TUNE_SPREAD_PLANES] = pl;
             if (nr) in[NFFT_TUNE_RHS_PER_GROUP] = nr;
@@ -1602,11 +1617,11 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
             // the register-tile kernels (modes 5, 7) take one rhs per work-group
             // and no LDS tile layout
             if ((md == 5 || md == 7) && (nr > 1 || pl != planes[0])) continue;
-            // the library's own choice has one shape; mode 7 for d = 2 has the
-            // tile shape (64 and 128 threads, any thread count in float64) and in
+            // mode 7 for d = 2 has the tile shape (64 and 128 threads) and in
             // float32 two more
-            if (md == 0 && (nr > 1 || nt != threads[0] || pl != planes[0])) continue;
-            if (md == 7 && d == 2 && nt != threads[0] && (!f32 || nt == 128)) continue;
+            if (md == 7 && d == 2 && f32 && nt == 128) continue;
+            if (d >= 2 && !(d == 2 && f32) && nt != threads[0] &&
+                (md != 1 || nr > 1 || default_choice(p, nrhs) == nfft::TileChoice::kLds)) continue;
             // the gather (mode 6) has one shape; 768 entries per unit are for it alone
             if (md == 6 && (nr > 1 || pl != planes[0] || nt != threads[0])) continue;
             if (K == 768 && md != 6) continue;
@@ -1620,7 +1635,7 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
             if (resolve_tuning(d, Ms, m, precision, in, NFFT_TUNE_COUNT, res, nullptr) != NFFT_OK)
               continue;
             std::copy(res, res + NFFT_TUNE_COUNT, p->tune);
-            p->asked = md == 0 && d == 2 ? 0 : 1u << NFFT_TUNE_SPREAD_MODE;
+            p->asked = asked_knobs(res, NFFT_TUNE_COUNT, d);
             const double t = time_adjoint(p, f, fhat, nrhs, s);
             if (t < 0) continue;
             if (best_t < 0 || t < best_t) {
