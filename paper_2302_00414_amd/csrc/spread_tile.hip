@@ -468,12 +468,16 @@ bool spread_tile_supported(int d, int T, int m) {
 //
 // Items: joining up to two saves the sum of split tiles, but doubles the chain
 // of chunks that a work-group takes one after the other (float64, m = 6: 6 us, m
-// = 8: 8). It pays where no tile stays split and the chain grows by one chunk at
-// most (16 tiles of 256 uniform nodes, m = 6, 20.4 -> 18.8; of 512 20.4 -> 26.8)
-// or the device is full all the same (4096 tiles of 256 127 -> 99.5), and from
-// three default items per compute unit on (m = 8: 130464 polar nodes on 224
-// tiles 37.4 -> 38.5, 261936 on 856 55.2 -> 55.4, 2097152 uniform ones on 4096
-// 284 -> 233).
+// = 8: 8). With few work-groups it pays while the chain grows by one chunk, in
+// float32 (sixteen staging waves up to m = 7) by two (float64, m = 6, 16 tiles of
+// 256 uniform nodes 20.4 -> 18.8, of 512 20.4 -> 26.8; float32, 371 a tile
+// 17.2 -> 16.7). Where the default items are about one work-group per compute
+// unit or more and the joined ones are at most that, also with longer chains
+// (256 tiles, half the nodes in half of them, longest 351 26.2 -> 23.4, 492 25.9 ->
+// 26.5; all alike, 503 30.6 -> 26.8), with the device full of joined items always
+// (4096 tiles of 256 127 -> 99.5). Tiles that stay split: from three default
+// items per compute unit on (m = 8: 130464 polar nodes on 224 tiles 37.4 -> 38.5,
+// 261936 on 856 55.2 -> 55.4, 2097152 uniform ones on 4096 284 -> 233).
 //
 // Kernel: while the LDS kernel has up to two work-groups per compute unit
 // (float64 at m = 8: 300), the longest item is the time of either kernel, with
@@ -481,7 +485,7 @@ bool spread_tile_supported(int d, int T, int m) {
 // float64, few: m = 3, longest 217 15.1 > 16.0, 256 19.2 > 19.4, 289 (joined)
 // 19.0 > 17.5; m = 4, 148 14.2 > 14.5, 217 16.3 > 16.2; m = 6, 71 13.1 > 13.7,
 // 104 14.5 > 14.0; m = 8, 256 on a spiral 26.7 > 27.4 and on uniform nodes 27.2 >
-// 24.5: the LDS kernel. Many: m = 3, mean 192 76.6 > 79.1, 256 (joined) 107 >
+// 24.5: the LDS kernel but for joined items, 298 26.2 > 27.1 and 296 26.8 > 23.3. Many: m = 3, mean 192 76.6 > 79.1, 256 (joined) 107 >
 // 92.8; m = 4, 64 25.0 > 25.6, 96 28.1 > 27.9; m = 6, 22 48.6 > 51.6, 64 63.0 >
 // 59.4; m = 8, 96 94.7 > 95.5, 128 116 > 103. At m <= 2 never more than even.
 // float32, few: m = 4, longest 13 11.3 > 10.9, m = 2, 13 10.7 > 10.8, 104 13.4 >
@@ -491,19 +495,24 @@ bool spread_tile_supported(int d, int T, int m) {
 // 45.5 > 41.7; m = 4, 22 18.3 > 18.6 and 42.4 > 37.9; m = 8, 45 29.5 > 28.4.
 TileChoice spread_tile_choice(bool f64, int m, int64_t N, int nrhs, const ItemShape& items,
                               const ItemShape& joined) {
+  const int64_t wgs = (int64_t)items.n * nrhs;
   bool join = false;
   if (joined.n > 0) {
     const int pairs = (nrhs + 1) / 2;  // as the launch below groups them
     const int64_t groups = (int64_t)joined.n * pairs >= 512 ? pairs : nrhs;
-    join = joined.split ? N * groups >= 3 * 256 * 256
-                        : joined.longest <= 320 || (int64_t)joined.n * nrhs >= 2048 ||
-                              N * groups >= 3 * 256 * 256;
+    const bool dense = N * groups >= 3 * 256 * 256;
+    const bool quick = !f64 && m <= 7;
+    int chain = quick ? 400 : 320;
+    if (wgs >= 240) chain = quick && wgs <= 768 ? 512 : 400;
+    if (wgs >= 360 && 3 * N >= 2 * (int64_t)joined.longest * joined.n) chain = 512;
+    if (joined.n * groups >= 1024 || dense) chain = 512;
+    join = joined.split ? dense : joined.longest <= chain;
   }
   const ItemShape& it = join ? joined : items;
   const TileChoice tile = join ? TileChoice::kJoined : TileChoice::kItems;
-  const int64_t wgs = (int64_t)items.n * nrhs;
   int least;
   if (wgs <= (f64 && m == 8 ? 300 : 512)) {
+    if (f64 && m == 8) return join ? tile : TileChoice::kLds;
     static const int longest64[9] = {0, 513, 513, 256, 160, 160, 100, 100, 513};
     static const int longest32[9] = {0, 128, 128, 0, 0, 0, 0, 0, 513};
     least = (f64 ? longest64 : longest32)[m];

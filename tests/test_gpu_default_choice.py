@@ -74,6 +74,30 @@ def test_default_spreading_is_not_slower_than_the_lds_kernel(prec, kind, M, N, m
     default, lds = _times(calls)
     print(f"[time] default {default:.1f} us, LDS kernel {lds:.1f} us", flush=True)
     assert default <= 1.1 * lds
+    calls.clear()
+    for p in plans:
+        p.close()
+
+
+@pytest.mark.parametrize("prec,M,N,m", [("f64", 128, 76800, 6), ("f64", 256, 1024 * 300, 6),
+                                        ("f32", 128, 76800, 6)])
+def test_default_items_are_joined_where_that_is_faster(prec, M, N, m):
+    """About 300 nodes in every tile: two items each and a sum, or one."""
+    from paper_2302_00414_amd.nfft import Plan
+    print(f"[case] joined N={N} M={M} m={m} {prec}", flush=True)
+    x = wl.uniform_nodes(N, 2, 1)
+    calls, plans = [], []
+    for tuning in (None, {"spread_mode": 7, "item_nodes": 512, "spread_threads": 64}):
+        p = Plan(x, M, 2.0, m, precision=prec, tuning=tuning)
+        p.set_weights(np.full(N, 1.0 / N))
+        v = torch.randn(N, dtype=p.cdtype, device="cuda")
+        out = torch.empty(1, M * M, dtype=p.cdtype, device="cuda")
+        plans.append(p)
+        calls.append(lambda p=p, v=v, out=out: p.adjoint(v, out=out))
+    default, joined = _times(calls)
+    print(f"[time] default {default:.1f} us, items of 512 {joined:.1f} us", flush=True)
+    assert default <= 1.1 * joined
+    calls.clear()
     for p in plans:
         p.close()
 
