@@ -197,11 +197,10 @@ __global__ __launch_bounds__(256) void spread3_mma_kernel(SpreadArgs<R> a) {
       last = max(last, __shfl_xor(last, 2));
       const int k0 = (max(first - wave, 0) + 3) >> 2;
       const int k1 = (last - wave) >> 2;  // -1 before this wave's first plane
-      mask = ((2 << k1) - 1) & ~((1 << k0) - 1);
-      if (last < wave) mask = 0;
+      mask = ((1 << (k1 + 1)) - 1) & ~((1 << k0) - 1);
     }
     __syncthreads();
-    load_chunk(b0 + NN);
+    if (b0 + NN < cnt) load_chunk(b0 + NN);
 
     const R* pb = opb;
     const R* pa = opa;
