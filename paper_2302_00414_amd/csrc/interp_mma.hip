@@ -24,7 +24,8 @@
 // reads (2m)^2 cells per node from LDS and evaluates the window again for
 // every right-hand side; here a work-group keeps NR tiles in LDS and one
 // evaluation serves all of them. Spiral of 131072 nodes, M = 256, m = 6, 32
-// right-hand sides: 217 -> 129 us; polar set of 262144 nodes, one: 17.2 -> 16.0.
+// right-hand sides: 217 -> 129 us; polar set of 262144 nodes, one, in the traces
+// 15.6 -> 15.5 (forward) and 17.0 -> 16.6 (refinement).
 #include "spread_common.hpp"
 
 namespace nfft {
@@ -32,28 +33,6 @@ namespace nfft {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
-
-// Lanes 0..31: a summed over the wave's halves, lanes 32..63: b.
-__device__ __forceinline__ float sum32(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// Even 16-lane rows: a summed over each pair of rows, odd rows: b.
-__device__ __forceinline__ float sum16(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// Lanes 0..31: the value of lane + 32.
-__device__ __forceinline__ float upper(float a) {
-  return __uint_as_float(
-      __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false)[1]);
-}
-
-// element i of p: a uniform base and a 32-bit byte offset per lane
-template <typename T>
-__device__ __forceinline__ T at(const T* p, uint32_t i) {
-  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + i * (uint32_t)sizeof(T));
-}
 
 constexpr int kInterpT = 16;
 constexpr int kInterpWaves = 4;
@@ -93,14 +72,6 @@ struct InterpShape {
   static constexpr size_t tile = (size_t)P * PS * sizeof(float2);
   static constexpr size_t factors = (size_t)kInterpWaves * (FN + RN) * sizeof(float);
 };
-
-// The factor rows a wave has written are read by its other lanes: the LDS
-// operations of a wave complete in order, so it is enough that the compiler
-// keeps them in order.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 }  // namespace
 

@@ -198,4 +198,35 @@ __device__ __forceinline__ void prep_node_pre(NodePrep<R, K2>& h, const R* q, R 
   h.q1 = pr.y;
 }
 
+// ----------------------------------------------- matrix-core window sums
+// Lanes 0..31: a summed over the wave's halves, lanes 32..63: b.
+__device__ __forceinline__ float sum32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Even 16-lane rows: a summed over each pair of rows, odd rows: b.
+__device__ __forceinline__ float sum16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Lanes 0..31: the value of lane + 32.
+__device__ __forceinline__ float upper(float a) {
+  return __uint_as_float(
+      __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false)[1]);
+}
+
+// element i of p: a uniform base and a 32-bit byte offset per lane
+template <typename T>
+__device__ __forceinline__ T at(const T* p, uint32_t i) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + i * (uint32_t)sizeof(T));
+}
+
+// LDS that a wave has written is read by its other lanes: the LDS operations
+// of a wave complete in order, so it is enough that the compiler keeps them in
+// order.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 }  // namespace nfft

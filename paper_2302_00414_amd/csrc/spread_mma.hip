@@ -34,8 +34,7 @@ namespace {
 // The accumulator block of v_mfma_f32_16x16x4 (four elements a lane, column
 // l & 15 of the 16 x 16 block, row 4 (l >> 4) + v for element v of lane l),
 // the operation, and a lane read.
-template <typename R> struct MmaT;
-template <> struct MmaT<float> {
+struct MmaT {
   typedef float v4 __attribute__((ext_vector_type(4)));
   static __device__ __forceinline__ v4 mfma(float a, float b, v4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -44,6 +43,7 @@ template <> struct MmaT<float> {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_addr, __float_as_int(v)));
   }
 };
+
 // y0, y1, Re c, Im c of a staged node
 template <typename R> struct alignas(4 * sizeof(R)) MmaNode {
   R y0, y1, cx, cy;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(64 * NW) void spread_mma_kernel(SpreadArgs<R> a) {
   constexpr int NT = 64 * NW;
   constexpr int NB = kMmaBatch;
   constexpr int DEG = PolyDeg<R>::value;
-  typedef typename MmaT<R>::v4 v4;
+  typedef MmaT::v4 v4;
   static_assert(K2 + 1 <= 16, "the rows of one tile row's nodes fit in 16 slots");
   static_assert((P * P) % 2 == 0 && P % 2 == 0, "tiles are summed two cells at a time");
   extern __shared__ double lds_d[];
@@ -174,18 +174,18 @@ __global__ __launch_bounds__(64 * NW) void spread_mma_kernel(SpreadArgs<R> a) {
         const R h0 = horner<R>(cf, nd.y0);
         const R h1 = horner<R>(cf, nd.y1);
         // row factor of slot j, column factors of padded columns j and 16 + j
-        const R ra = MmaT<R>::read(h0, addrA);
+        const R ra = MmaT::read(h0, addrA);
         const int qB = j + qoff;
-        const R cb = MmaT<R>::read(h1, (lrow | (qB & 15)) << 2);
+        const R cb = MmaT::read(h1, (lrow | (qB & 15)) << 2);
         const R A = inA ? ra : (edA ? ne.x : (R)0);
         const R B0 = (unsigned)qB < (unsigned)K2 ? cb : (qB == -1 ? ne.y : (R)0);
         const R B1 = qB < K2 - 16 ? cb : (R)0;
         const R ar = A * nd.cx;
         const R ai = A * nd.cy;
-        acc0r = MmaT<R>::mfma(ar, B0, acc0r);
-        acc1r = MmaT<R>::mfma(ar, B1, acc1r);
-        acc0i = MmaT<R>::mfma(ai, B0, acc0i);
-        acc1i = MmaT<R>::mfma(ai, B1, acc1i);
+        acc0r = MmaT::mfma(ar, B0, acc0r);
+        acc1r = MmaT::mfma(ar, B1, acc1r);
+        acc0i = MmaT::mfma(ai, B0, acc0i);
+        acc1i = MmaT::mfma(ai, B1, acc1i);
       }
       gbase += ng;
       // padded row r is complete for this wave: slot r (accumulator element
