@@ -374,7 +374,7 @@ def run_jittered3d(steps, precs=("f32", "f64"), tuning="auto"):
             # the spreading stage against the float32 peak: (2m)^3 window
             # cells per node, a complex sample times a real factor
             fl = spread_flops(N, m3, 3)
-            mfma = plan.tuning()["spread_mode"] == 7
+            mfma = on_matrix_cores(plan.tuning())
             res[prec]["spread_roofline"] = dict(
                 bound="mfma" if mfma else "alu", achieved=round(fl / (us * 1e-6) / 1e12, 3),
                 peak=FP32_PEAK_TFLOPS, unit="TFLOP/s",
@@ -526,7 +526,7 @@ def run_batched(steps, precs=("f32", "f64"), tuning="auto"):
             fl = spread_flops(N, MW, D) * R
             if us > 0:
                 res[prec]["spread_roofline"] = dict(
-                    bound="mfma" if plan.tuning()["spread_mode"] in (6, 7) else "alu",
+                    bound="mfma" if on_matrix_cores(plan.tuning()) else "alu",
                     achieved=round(fl / (us * 1e-6) / 1e12, 3), peak=FP32_PEAK_TFLOPS,
                     unit="TFLOP/s", frac=round(fl / (us * 1e-6) / 1e12 / FP32_PEAK_TFLOPS, 4),
                     algorithmic_flops=fl, us=round(us, 2))
@@ -628,6 +628,16 @@ SPREAD_SOURCES = ("spread.hip", "spread_common.hpp", "spread_group.hpp", "spread
                   "spread_rows.hip", "spread_reg.hip", "spread_mma.hip", "spread_tile.hip")
 
 
+def library_choice(t):
+    """Whether this tuning leaves the spreading kernel to the library (which
+    takes a matrix-core kernel on the workloads here)."""
+    return t["spread_mode"] == 1 and t["spread_threads"] == 128 and t["spread_planes"] == 1
+
+
+def on_matrix_cores(t):
+    return t["spread_mode"] in (6, 7) or library_choice(t)
+
+
 def spread_kernel_name(t):
     """Name of the spreading kernel the library launches for this tuning
     (d = 2, m = 6, float32, one right-hand side), as the profiler prints it."""
@@ -639,6 +649,8 @@ def spread_kernel_name(t):
         if mode == 7:
             return f"spread_mma_kernel<float, {MW}, {nw}>" if nw > 2 else f"spread_tile_kernel<float, {MW}, 1, 1>"
         return f"spread_reg_kernel<{MW}, {nw}>"
+    if library_choice(t) and T == 16:
+        return f"spread_tile_kernel<float, {MW}, 1, 1>"   # on a full device
     ws = {3: 1, 4: 2}.get(mode, 0)   # window source of the group kernel
     return (f"spread_group_kernel<float, 2, {MW}, {t['spread_threads']}, "
             f"{T if T in (8, 16) else 0}, {'true' if t['spread_planes'] == 2 else 'false'}, {ws}>")
@@ -733,7 +745,7 @@ def main():
     kname = spread_kernel_name(t)
     # modes 6 and 7 form the sums on the matrix cores (float32 MFMA peak,
     # the same figure as the vector peak); the others on the vector ALUs
-    roofline = dict(bound="mfma" if t["spread_mode"] in (6, 7) else "alu",
+    roofline = dict(bound="mfma" if on_matrix_cores(t) else "alu",
                     achieved=round(achieved, 3), peak=FP32_PEAK_TFLOPS,
                     unit="TFLOP/s", frac=round(achieved / FP32_PEAK_TFLOPS, 5),
                     traffic=traffic_record(kname),

@@ -1620,8 +1620,12 @@ int nfft_plan_autotune(nfft_plan_t* out, int d, int M, double sigma, int m, int6
             // mode 7 for d = 2 has the tile shape (64 and 128 threads) and in
             // float32 two more
             if (md == 7 && d == 2 && f32 && nt == 128) continue;
+            const nfft::TileChoice dc = default_choice(p, nrhs);
             if (d >= 2 && !(d == 2 && f32) && nt != threads[0] &&
-                (md != 1 || nr > 1 || default_choice(p, nrhs) == nfft::TileChoice::kLds)) continue;
+                (md != 1 || nr > 1 || dc == nfft::TileChoice::kLds)) continue;
+            // the library's choice where it is what mode 7 runs
+            if (md == 1 && dc == nfft::TileChoice::kItems && nr <= 1 && (!nt || nt == 128) && pl <= 1 &&
+                (d == 3 || m <= 7)) continue;
             // the gather (mode 6) has one shape; 768 entries per unit are for it alone
             if (md == 6 && (nr > 1 || pl != planes[0] || nt != threads[0])) continue;
             if (K == 768 && md != 6) continue;

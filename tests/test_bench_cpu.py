@@ -40,6 +40,13 @@ def test_kernel_names_follow_the_tuning():
         "spread_reg_kernel<6, 8>"
 
 
+def test_kernel_name_of_the_default_tuning():
+    t = {"tile_edge": 16, "spread_mode": 1, "spread_threads": 128, "spread_planes": 1}
+    assert bench.spread_kernel_name(t) == "spread_tile_kernel<float, 6, 1, 1>"
+    assert bench.spread_kernel_name(dict(t, spread_threads=64)) == \
+        "spread_group_kernel<float, 2, 6, 64, 16, false, 0>"
+
+
 def test_traffic_record_is_tied_to_the_sources():
     """The counter summary under profiles/ is reported as the kernel's HBM
     traffic only while the spreading sources are the ones it was taken on
