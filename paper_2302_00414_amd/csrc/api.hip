@@ -321,7 +321,8 @@ int resolve_tuning(int d, int Ms, int m, int precision, const int* in, int n, in
   const bool f64 = precision == NFFT_F64;
   const size_t one = mode == 6   ? nfft::spread_gather_lds_bytes(m)
                      : mode == 7 && d == 3 ? nfft::spread3_mma_lds_bytes(f64)
-                     : mode == 7 ? std::max(f64 ? 0 : nfft::spread_mma_lds_bytes(m, nt), nfft::spread_tile_lds_bytes(m, f64))
+                     : mode == 7 ? std::max(f64 ? 0 : nfft::spread_mma_lds_bytes(m, nt),
+                                            nfft::spread_tile_lds_bytes(m, f64))
                      : mode == 5 ? nfft::spread_reg_lds_bytes(m)
                                  : nfft::spread_lds_bytes(d, f64, m, T, Ptot, nt, 1, planes);
   const size_t multi = out[NFFT_TUNE_RHS_PER_GROUP] > 1
@@ -827,7 +828,8 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   // Entries without nodes fill the last eighth.
   std::vector<int32_t> fitem;
   const bool f64 = p->prec == NFFT_F64;
-  if (nfft::interp_mma_supported(d, g.T, f64, p->m) || nfft::interp3_mma_supported(d, g.T, f64, p->m)) {
+  if (nfft::interp_mma_supported(d, g.T, f64, p->m) ||
+      nfft::interp3_mma_supported(d, g.T, f64, p->m)) {
     std::vector<int32_t> it;
     for (int b = 0; b < g.nbins; ++b) {
       const int n = hc[b], k = (n + nfft::kInterpItem - 1) / nfft::kInterpItem;
@@ -842,7 +844,8 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
     p->nfwd = 8 * per;
     fitem.assign((size_t)4 * p->nfwd, 0);
     for (int i = 0; i < n; ++i)
-      std::copy(it.begin() + 4 * i, it.begin() + 4 * i + 4, fitem.begin() + 4 * ((i % per) * 8 + i / per));
+      std::copy(it.begin() + 4 * i, it.begin() + 4 * i + 4,
+                fitem.begin() + 4 * ((i % per) * 8 + i / per));
   }
   HIP_TRY(p, hipMemcpyAsync(bstart, hstart.data(), (g.nbins + 1) * sizeof(int32_t),
                             hipMemcpyHostToDevice, s));

@@ -158,7 +158,8 @@ hipError_t launch_spread_tile(const SpreadArgs<R>& a, int nrhs, hipStream_t s);
 // dimension-0 cell within tiles), float32 or float64, and the default mode's
 // kernel where spread3_mma_preferred says so.
 bool spread3_mma_supported(int d, int T, bool f64, int m);
-bool spread3_mma_preferred(int d, int T, bool f64, int m, int64_t N, int nrhs, const ItemShape& items);
+bool spread3_mma_preferred(int d, int T, bool f64, int m, int64_t N, int nrhs,
+                           const ItemShape& items);
 size_t spread3_mma_lds_bytes(bool f64);
 template <typename R>
 hipError_t launch_spread3_mma(const SpreadArgs<R>& a, int nrhs, hipStream_t s);

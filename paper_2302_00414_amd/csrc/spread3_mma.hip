@@ -260,8 +260,10 @@ bool spread3_mma_supported(int d, int T, bool f64, int m) {
 // an item shows (three right-hand sides, 8192 nodes 90.3 > 93.7, 32768, eight a
 // tile, 99.3 > 102.0; one, 131072, 32 a tile, 58.6 > 51.2). At m = 1 a node
 // updates 8 cells and either may be the faster one.
-bool spread3_mma_preferred(int d, int T, bool f64, int m, int64_t N, int nrhs, const ItemShape& items) {
-  if (m == 2 && !f64 && (int64_t)items.n * nrhs >= 2048 && N < 16 * (int64_t)items.n) return false;
+bool spread3_mma_preferred(int d, int T, bool f64, int m, int64_t N, int nrhs,
+                           const ItemShape& items) {
+  if (m == 2 && !f64 && (int64_t)items.n * nrhs >= 2048 && N < 16 * (int64_t)items.n)
+    return false;
   return m >= 2 && spread3_mma_supported(d, T, f64, m);
 }
 

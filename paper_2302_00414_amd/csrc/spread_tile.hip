@@ -33,8 +33,10 @@
 // the closed-edge row is summed by vector operations beside it.
 //
 // Bound: matrix and vector work, which take turns (no cycle with both busy by
-// the counters): per group of four nodes 4 matrix operations and about 70
-// vector instructions, half of them the staging. Against mode 7's other shape
+// the counters): per group of four nodes 4 matrix operations (64 cycles each in
+// float64, 32 in float32) and 60 to 100 vector instructions, half of them the
+// staging. Linogram below at m = 8: 58 and 87 of 214 us, polar set at m = 6 in
+// float64 7.0 and 7.7 of 27, the rest waits of short chains. Against mode 7's other shape
 // (every wave its own padded tile of a quarter of the groups, summed in LDS
 // at the end), polar set of 262144 nodes, M = 256, float64, whole transforms:
 // m = 3 43.7 -> 34.3 us, m = 6 50.5 -> 40.0, m = 7 67.7 -> 49.3; float32,
@@ -166,8 +168,9 @@ __global__ __launch_bounds__(256 * NS) void spread_tile_kernel(SpreadArgs<R> a, 
   // from them both cells, lane 8 + p at its column offset. The last two steps
   // are Horner's, so that c_0, the largest term, enters in one rounding: float32
   // errors of whole transforms over the LDS kernel's 0.94 to 1.01, with the
-  // even part closed before the odd one is added 0.94 to 1.02. The entries past the window (its cells 2m .. 15: zeros and,
-  // as cell 15, the closed edge) fall to the lanes p >= m.
+  // even part closed before the odd one is added 0.94 to 1.02. The entries past
+  // the window (its cells 2m .. 15: zeros and, as cell 15, the closed edge) fall
+  // to the lanes p >= m.
   R ce[DEG / 2 + 1], co[DEG / 2];
   const R* pcf = a.coef + (jj < MW ? jj : 0) * (DEG + 1);
 #pragma unroll
@@ -485,9 +488,11 @@ bool spread_tile_supported(int d, int T, int m) {
 // float64, few: m = 3, longest 217 15.1 > 16.0, 256 19.2 > 19.4, 289 (joined)
 // 19.0 > 17.5; m = 4, 148 14.2 > 14.5, 217 16.3 > 16.2; m = 6, 71 13.1 > 13.7,
 // 104 14.5 > 14.0; m = 8, 256 on a spiral 26.7 > 27.4 and on uniform nodes 27.2 >
-// 24.5: the LDS kernel but for joined items, 298 26.2 > 27.1 and 296 26.8 > 23.3. Many: m = 3, mean 192 76.6 > 79.1, 256 (joined) 107 >
-// 92.8; m = 4, 64 25.0 > 25.6, 96 28.1 > 27.9; m = 6, 22 48.6 > 51.6, 64 63.0 >
-// 59.4; m = 8, 96 94.7 > 95.5, 128 116 > 103. At m <= 2 never more than even.
+// 24.5: the LDS kernel but for joined items (298 on a spiral 26.2 > 27.1, 296 on
+// uniform nodes 26.8 > 23.3). Many: m = 3, mean 192 76.6 > 79.1, 256 (joined)
+// 107 > 92.8; m = 4, 64 25.0 > 25.6, 96 28.1 > 27.9; m = 6, 22 48.6 > 51.6, 64
+// 63.0 > 59.4; m = 8, 96 94.7 > 95.5, 128 116 > 103. At m <= 2 about even at best
+// (joined, mean 256, m = 2 36.6 > 34.3 and 88.9 > 91.7): the LDS kernel.
 // float32, few: m = 4, longest 13 11.3 > 10.9, m = 2, 13 10.7 > 10.8, 104 13.4 >
 // 12.4; m = 8, 223 on a spiral 23.2 > 24.7, 256 27.2 > 26.5 but on other spirals
 // 0.98 of the LDS kernel: left to that. Many: m = 2, mean 192 23.3 > 24.1, 256
@@ -510,21 +515,21 @@ TileChoice spread_tile_choice(bool f64, int m, int64_t N, int nrhs, const ItemSh
   }
   const ItemShape& it = join ? joined : items;
   const TileChoice tile = join ? TileChoice::kJoined : TileChoice::kItems;
-  int least;
+  // from which longest or mean item on, by m; X: not at all
+  constexpr int X = 1 << 30;
   if (wgs <= (f64 && m == 8 ? 300 : 512)) {
+    static const int longest64[9] = {X, X, X, 256, 160, 160, 100, 100, X};
+    static const int longest32[9] = {X, 128, 128, 0, 0, 0, 0, 0, X};
     if (f64 && m == 8) return join ? tile : TileChoice::kLds;
-    static const int longest64[9] = {0, 513, 513, 256, 160, 160, 100, 100, 513};
-    static const int longest32[9] = {0, 128, 128, 0, 0, 0, 0, 0, 513};
-    least = (f64 ? longest64 : longest32)[m];
-    return it.longest >= least && least <= 512 ? tile : TileChoice::kLds;
+    return it.longest >= (f64 ? longest64 : longest32)[m] ? tile : TileChoice::kLds;
   }
-  static const int mean64[9] = {0, 513, 513, 200, 110, 110, 64, 64, 110};
-  static const int mean32[9] = {0, 200, 200, 64, 0, 0, 0, 0, 64};
-  least = (f64 ? mean64 : mean32)[m];
+  static const int mean64[9] = {X, X, X, 200, 110, 110, 64, 64, 110};
+  static const int mean32[9] = {X, 200, 200, 64, 0, 0, 0, 0, 64};
+  int64_t mean = (f64 ? mean64 : mean32)[m];
   // with tiles still split the sum of their slots takes the gain up to denser
   // sets (m = 2, mean 264 29.7 > 30.5, 342 47.9 > 41.5)
-  if (m <= 2 && it.split) least = m == 2 && !f64 && wgs >= 1280 ? 300 : 513;
-  return least <= 512 && N >= (int64_t)least * it.n ? tile : TileChoice::kLds;
+  if (m <= 2 && it.split) mean = m == 2 && !f64 && wgs >= 1280 ? 300 : X;
+  return N >= mean * it.n ? tile : TileChoice::kLds;
 }
 
 size_t spread_tile_lds_bytes(int m, bool f64) {
@@ -552,8 +557,9 @@ static hipError_t spread_tile_m(const SpreadArgs<R>& a, int nrhs, hipStream_t s)
   // At most one work-group per compute unit, of several chunks: nothing covers
   // the waits of a chunk's staging, so 16 waves stage four chunks at a time
   // (float32, whole transforms, against one at a time: 20001 nodes, M = 32,
-  // m = 4, 23.7 -> 21.2 us; 40321, M = 128, m = 6, 16.9 -> 16.0). Not at m = 8 (140000, M = 128: 32.1 -> 32.8), nor in
-  // float64, whose products cover them (4096, M = 32, m = 4: 18.4 -> 19.0).
+  // m = 4, 23.7 -> 21.2 us; 40321, M = 128, m = 6, 16.9 -> 16.0). Not at m = 8
+  // (140000, M = 128: 32.1 -> 32.8), nor in float64, whose products cover them
+  // (4096, M = 32, m = 4: 18.4 -> 19.0).
   if constexpr (std::is_same<R, float>::value && MW <= 7)
     if ((int64_t)a.g.nsub * nrhs <= 256 && a.g.N > (int64_t)kTileChunk * a.g.nsub)
       return spread_tile_nr<R, MW, 1, 4>(a, nrhs, s);

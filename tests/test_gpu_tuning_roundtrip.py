@@ -39,6 +39,9 @@ def test_a_reported_default_tuning_is_the_default(prec, d, M, N, m, nrhs, lds):
     t = p.tuning()
     q = _plan(x, M, m, prec, nrhs, t)
     assert q.tuning() == t
+    from paper_2302_00414_amd.nfft import nfft_footprint
+    for k in (p, q):
+        assert nfft_footprint(d, M, 2.0, m, N, prec, nrhs) >= k.info()["bytes"]
     v = torch.from_numpy(wl.complex_normal((nrhs, N), 2)).to(p.cdtype).cuda()
     a, b = torch.view_as_real(p.adjoint(v)), torch.view_as_real(q.adjoint(v))
     if lds and prec == "f64":
