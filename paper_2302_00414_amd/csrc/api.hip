@@ -777,10 +777,12 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
       ncu < 1)
     ncu = 256;
   auto launch_order = [&](const std::vector<int32_t>& count) {
-    std::vector<int32_t> order(count.size());
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t u, int32_t v) { return count[u] > count[v]; });
+    // stable, by count (an item has 65536 nodes at most)
+    const int top = *std::max_element(count.begin(), count.end());
+    std::vector<int32_t> order(count.size()), at(top + 2, 0);
+    for (int32_t c : count) ++at[top - c + 1];
+    std::partial_sum(at.begin(), at.end(), at.begin());
+    for (size_t i = 0; i < count.size(); ++i) order[at[top - count[i]]++] = (int32_t)i;
     const size_t C = (size_t)ncu;
     for (size_t b0 = C; b0 < order.size(); b0 += 2 * C)
       std::reverse(order.begin() + b0, order.begin() + std::min(order.size(), b0 + C));
@@ -885,30 +887,30 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
                                         (const R*)frac2, p->perm, p->loc, (R*)p->frac, s));
   }
 
-  auto upload = [&](const std::vector<int32_t>& h, int32_t** q) {
-    TRY(dalloc(p, q, std::max<size_t>(1, h.size()) * sizeof(int32_t)));
-    if (!h.empty())
-      HIP_TRY(p, hipMemcpyAsync(*q, h.data(), h.size() * 4, hipMemcpyHostToDevice, s));
-    return (int)NFFT_OK;
+  // the tables in one allocation and one copy, each from a 16-byte boundary on
+  std::vector<int32_t> tables;
+  std::vector<std::pair<int32_t**, size_t>> places;
+  auto place = [&](const std::vector<int32_t>& h, int32_t** q) {
+    places.push_back({q, tables.size()});
+    tables.insert(tables.end(), h.begin(), h.end());
+    tables.resize((tables.size() + 3) / 4 * 4, 0);
   };
-  auto upload_items = [&](const HostItems& h, ItemTable& t) {
-    TRY(upload(h.start, &t.start));
-    TRY(upload(h.count, &t.count));
-    TRY(upload(h.bin, &t.bin));
-    TRY(upload(h.slot, &t.slot));
-    TRY(upload(h.multi_bin, &t.multi_bin));
-    return upload(h.multi_first, &t.multi_first);
+  auto place_items = [&](const HostItems& h, ItemTable& t) {
+    place(h.start, &t.start);
+    place(h.count, &t.count);
+    place(h.bin, &t.bin);
+    place(h.slot, &t.slot);
+    place(h.multi_bin, &t.multi_bin);
+    place(h.multi_first, &t.multi_first);
   };
-  TRY(upload_items(hitems, p->items));
-  if (p->joined.n) TRY(upload_items(hjoined, p->joined));
-  TRY(dalloc(p, &p->empty_bins, std::max<size_t>(1, ebins.size()) * sizeof(int32_t)));
-  if (!ebins.empty())
-    HIP_TRY(p, hipMemcpyAsync(p->empty_bins, ebins.data(), ebins.size() * 4, hipMemcpyHostToDevice, s));
-
-  if (!fitem.empty()) {
-    TRY(dalloc(p, &p->fwd_items, fitem.size() * sizeof(int32_t)));
-    HIP_TRY(p, hipMemcpyAsync(p->fwd_items, fitem.data(), fitem.size() * 4, hipMemcpyHostToDevice, s));
-  }
+  place_items(hitems, p->items);
+  if (p->joined.n) place_items(hjoined, p->joined);
+  place(ebins, &p->empty_bins);
+  place(fitem, &p->fwd_items);
+  int32_t* dtables;
+  TRY(dalloc(p, &dtables, tables.size() * sizeof(int32_t)));
+  HIP_TRY(p, hipMemcpyAsync(dtables, tables.data(), tables.size() * 4, hipMemcpyHostToDevice, s));
+  for (const auto& pl : places) *pl.first = dtables + pl.second;
   TRY(dalloc(p, &p->w, (N + pad) * sizeof(cplx<R>)));
   HIP_TRY(p, hipMemsetAsync((cplx<R>*)p->w + N, 0, pad * sizeof(cplx<R>), s));
   TRY(alloc_workspace<R>(p, s));
@@ -1418,6 +1420,7 @@ int64_t nfft_footprint(int d, int M, double sigma, int m, int64_t N, int precisi
   const bool f64 = precision == NFFT_F64;
   if (nfft::interp_mma_supported(d, T, f64, m) || nfft::interp3_mma_supported(d, T, f64, m))
     bytes += (nbins + N / nfft::kInterpItem + 8) * 16;    // forward work items
+  bytes += 14 * 16;                                       // the tables' alignment
   if (nfft::spread_tile_supported(d, T, m))               // the joined spreading items
     bytes += (nbins + N / (2 * K) + 1) * 4 * 4 + (2 * nbins + 1) * 4;
   return bytes;
