@@ -170,6 +170,7 @@ struct nfft_plan_s {
   bool join = false;               // whether to keep the joined items
   int32_t* fwd_items = nullptr;    // forward window sums on the matrix cores, if supported:
                                    // [nfwd][4] first node, nodes, tile, 0
+  int32_t* fwd_lane = nullptr;     // one lane a node: the spreading's items, [items.n][4]
   int nfwd = 0;
   int32_t* empty_bins = nullptr;   // tiles without nodes (their slots are never written)
   void* gpart = nullptr;           // spread mode 6 partials [max_rhs][slot][256]
@@ -849,6 +850,10 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
       std::copy(it.begin() + 4 * i, it.begin() + 4 * i + 4,
                 fitem.begin() + 4 * ((i % per) * 8 + i / per));
   }
+  // the lane-per-node form takes the spreading's items, in one load each
+  std::vector<int32_t> flane;
+  for (int i = 0; i < p->items.n; ++i)
+    flane.insert(flane.end(), {hitems.start[i], hitems.count[i], hitems.bin[i], 0});
   HIP_TRY(p, hipMemcpyAsync(bstart, hstart.data(), (g.nbins + 1) * sizeof(int32_t),
                             hipMemcpyHostToDevice, s));
   p->shared->hbin_start = hstart;
@@ -907,6 +912,7 @@ int build_plan(nfft_plan_t p, const double* nodes, hipStream_t s) {
   if (p->joined.n) place_items(hjoined, p->joined);
   place(ebins, &p->empty_bins);
   place(fitem, &p->fwd_items);
+  place(flane, &p->fwd_lane);
   int32_t* dtables;
   TRY(dalloc(p, &dtables, tables.size() * sizeof(int32_t)));
   HIP_TRY(p, hipMemcpyAsync(dtables, tables.data(), tables.size() * 4, hipMemcpyHostToDevice, s));
@@ -1210,9 +1216,7 @@ int run_forward(nfft_plan_t p, const void* fhat, void* f, int nrhs, hipStream_t 
   ia.grid = (const cplx<R>*)p->grid;
   ia.f = (cplx<R>*)f;
   ia.sub = (const cplx<R>*)sub;
-  ia.item_start = p->items.start;
-  ia.item_count = p->items.count;
-  ia.item_bin = p->items.bin;
+  ia.lane_items = p->fwd_lane;
   ia.items = p->fwd_items;
   ia.nitems = p->nfwd;
   ia.coef = (const R*)p->coef;
@@ -1420,7 +1424,8 @@ int64_t nfft_footprint(int d, int M, double sigma, int m, int64_t N, int precisi
   const bool f64 = precision == NFFT_F64;
   if (nfft::interp_mma_supported(d, T, f64, m) || nfft::interp3_mma_supported(d, T, f64, m))
     bytes += (nbins + N / nfft::kInterpItem + 8) * 16;    // forward work items
-  bytes += 14 * 16;                                       // the tables' alignment
+  bytes += nsub_max * 16;                                 // forward items, one lane a node
+  bytes += 15 * 16;                                       // the tables' alignment
   if (nfft::spread_tile_supported(d, T, m))               // the joined spreading items
     bytes += (nbins + N / (2 * K) + 1) * 4 * 4 + (2 * nbins + 1) * 4;
   return bytes;

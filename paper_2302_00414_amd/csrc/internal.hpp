@@ -193,9 +193,7 @@ struct InterpArgs {
   const cplx<R>* grid;       // full oversampled grid, C order, rhs stride grid_rs
   cplx<R>* f;                // output samples, caller order, rhs stride f_rs
   const cplx<R>* sub;        // if set: f = sub - (window sums), sub in caller order, stride f_rs
-  const int32_t* item_start; // work items of the spreading (g.nsub)
-  const int32_t* item_count;
-  const int32_t* item_bin;
+  const int32_t* lane_items; // one lane a node: [g.nsub][4] first node, nodes, tile, 0
   const int32_t* items;      // matrix cores: [nitems][4] first node, nodes (0: padding), tile, 0
   int nitems;
   const R* coef;

@@ -344,7 +344,7 @@ template <typename R, int D, int MW>
 __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   extern __shared__ unsigned char smem_raw[];
   cplx<R>* tile = reinterpret_cast<cplx<R>*>(smem_raw);
-  const int item = blockIdx.x;
+  const int4 it = reinterpret_cast<const int4*>(a.lane_items)[blockIdx.x];
   const int rhs = blockIdx.y;
   const int P = a.g.P;
   const int Ptot = a.g.Ptot;
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   // tile origin (in cells) of this work item's tile, per dimension
   int org[3] = {0, 0, 0};
   {
-    int bb = a.item_bin[item];
+    int bb = it.z;
     for (int t = D - 1; t >= 0; --t) {
       org[t] = (bb % nb) * a.g.T - a.g.m;
       bb /= nb;
@@ -393,8 +393,7 @@ __global__ __launch_bounds__(256) void interp_kernel(InterpArgs<R> a) {
   __syncthreads();
 
   const int64_t N = a.g.N;
-  const int start = a.item_start[item];
-  const int cnt = a.item_count[item];
+  const int start = it.x, cnt = it.y;
   cplx<R>* f = a.f + rhs * a.f_rs;
   for (int k = threadIdx.x; k < cnt; k += blockDim.x) {
     const int i = start + k;
