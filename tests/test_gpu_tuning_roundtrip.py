@@ -68,3 +68,27 @@ def test_autotuned_plan_is_not_slower_than_the_default(prec, M, N, m):
     assert t[1] <= 1.1 * t[0] and t[2] <= 1.1 * t[1]
     for k in (p, q, r):
         k.close()
+
+
+def test_autotuner_times_the_gathers_longest_units_at_speed():
+    """32 spiral right-hand sides in one call: units of 768 list entries take
+    140 us, of 512 150; timed straight after its plan's making the 768 candidate
+    read 147 as the 512 one did, and one plan in five got the slower. Graph
+    replays timed in turn repeat to 1 % and the two are 7 % apart: 1.03."""
+    M, N = 256, 131072
+    x = wl.spiral_nodes(N, M)
+    v = torch.from_numpy(wl.complex_normal((32, N), 2)).to(torch.complex64).cuda()
+    out = torch.empty(32, M * M, dtype=torch.complex64, device="cuda")
+    got = []
+    for i in range(8):
+        p = _plan(x, M, 6, "f32", 32, "auto")
+        got.append(p.tuning())
+        p.close()
+        print(f"[case] auto spiral, 32 rhs, {i}: {got[-1]}", flush=True)
+    best = {"tile_edge": 16, "item_nodes": 768, "fft_min_wg": 64, "spread_mode": 6}
+    plans = [_plan(x, M, 6, "f32", 32, t) for t in [best] + [dict(t) for t in {tuple(t.items()) for t in got}]]
+    t = _times([lambda k=k: k.adjoint(v, out=out) for k in plans])
+    print(f"[time] {[round(k, 1) for k in t]} us", flush=True)
+    assert max(t) <= 1.03 * t[0]
+    for k in plans:
+        k.close()
